@@ -75,6 +75,7 @@ struct LargeArgs {
     double* ll_scratch;   // [1] log-likelihood slot when the caller wants intensities only
     bool carry_prefix;    // carry_seg holds in-group prefixes (the scan's apply pass left out)
     double *gpart, *spart, *cpart_;  // [ER][M][M]; [ER][M] per target, [NRUN][M] shared decay
+    double* csum;         // [M] the columns' compensator sums (shared decay, gradient)
     double* gsup;         // [min(8, ER)][M*M] support-restricted first term of eq. 9 in CSR order (the
                           //   first nnz(alpha) entries of each copy; shares gpart's space)
     int64_t nslot;        // checkpoint slots
@@ -155,6 +156,11 @@ void bucket_chunk_into(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg,
 // ck_only: the checkpoint kernel alone (its per-column sums of dL/dmu and
 // the compensator), for the support-restricted gradient
 void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipStream_t st, bool ck_only);
+
+// final sums and outputs of kernel k (see large_final); csum: the columns' compensator sums, or null
+void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,
+                        const double* spart, const double* cpart, double* g_alpha, double* csum, int32_t k,
+                        hipStream_t st);
 
 size_t seq_workspace_bytes(const hawkes_problem* p);
 hawkes_status run_sequential(const hawkes_problem* p, const double* t, const int32_t* marks, const float* mu,

@@ -1229,45 +1229,6 @@ __global__ __launch_bounds__(64 * HK_DWP) void pt_dense(int64_t c0, int64_t c1, 
     if (rb == 0 && s0 + lane < M) npart[(int64_t)er * M + s0 + lane] += nl;
 }
 
-__global__ __launch_bounds__(256) void pt_final(int32_t M, int32_t ER, double T, const float* __restrict__ mu,
-                         const double* __restrict__ acc, const double* __restrict__ gpart,
-                         const double* __restrict__ spart, const double* __restrict__ npart,
-                         const double* __restrict__ ebacc,
-                         double* __restrict__ loglik, double* __restrict__ g_mu, double* __restrict__ g_alpha,
-                         double* __restrict__ g_beta, int grad) {
-    const int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t MM = (int64_t)M * M;
-    if (blockIdx.x == 0) {
-        // sum of mu in a fixed order: strided partial sums, then a tree
-        __shared__ double ps[256];
-        double v = 0.0;
-        for (int32_t p = threadIdx.x; p < M; p += 256) v += (double)mu[p];
-        ps[threadIdx.x] = v;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) ps[threadIdx.x] += ps[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) loglik[0] = acc[0] - T * ps[0] - acc[1];
-    }
-    if (!grad) return;
-    if (x < MM && g_alpha) {
-        const int32_t q = (int32_t)(x % M);
-        double g = 0.0, c = 0.0;
-        for (int32_t e = 0; e < ER; ++e) {
-            g += gpart[(int64_t)e * MM + x];
-            c += npart[(int64_t)e * M + q];
-        }
-        g_alpha[x] = g - c;
-    }
-    if (x < M) {
-        double s = 0.0;
-        for (int32_t e = 0; e < ER; ++e) s += spart[(int64_t)e * M + x];
-        if (g_mu) g_mu[x] = s - T;
-        if (g_beta) g_beta[x] = -ebacc[x];
-    }
-}
-
 // ------------------------------------------------------------------ host
 hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
     const int32_t M = A.M;
@@ -1445,10 +1406,7 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
             }
         }
     }
-    const int64_t nfin = A.grad ? (MM > M ? MM : M) : 1;
-    hipLaunchKernelGGL(pt_final, dim3((unsigned)((nfin + 255) / 256)), dim3(256), 0, st, M, A.ER, A.T, A.mu, A.acc,
-                       A.gpart, A.spart, A.cpart_, A.ebacc, A.loglik, A.g_mu, A.g_alpha, A.g_beta,
-                       A.grad ? 1 : 0);
+    large_final_launch(A, A.ER, A.ebacc, A.gpart, A.spart, A.cpart_, A.g_alpha, nullptr, 0, st);
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
