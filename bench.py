@@ -536,7 +536,7 @@ def main() -> int:
         flops_per_launch = 2.0 * w.M * (w.n * args.steps / dense_n)
         achieved = flops_per_launch / (avg_ms * 1e-3) / 1e12
         tr = load_traffic(src, tuning)
-        roofline = {"kernel": "large_dense (dense dL/dalpha)", "bound": "alu", "achieved": round(achieved, 3),
+        roofline = {"kernel": "dense_tiles (dense dL/dalpha)", "bound": "alu", "achieved": round(achieved, 3),
                     "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4),
                     "traffic": (tr["bytes_per_launch"] if tr else None),

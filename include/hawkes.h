@@ -39,7 +39,9 @@
  *    (state, decays, intensities, log-likelihood and the dL/dmu, dL/dbeta
  *    terms) is float64 in every mode.  The dense dL/dalpha kernels keep a
  *    float64 state and float64 accumulators with float32 decay factors
- *    (each exponent is formed and range-reduced in float64).
+ *    (each exponent is formed and range-reduced in float64); from 384 nodes on
+ *    the state between blocks of events enters in float32, in float32 sums of
+ *    at most 128 blocks.
  *    Every sum over events (log-likelihood, gradients) is accumulated in
  *    float64 in a fixed order, so repeated calls return bitwise-identical
  *    results, with one exception: in the large-M engine, dL/dalpha sums its
@@ -113,22 +115,18 @@ typedef struct hawkes_problem {
  * it is too small).  Set it between calls, not while calls run on other
  * threads.  Intended for callers that time candidate values on their own
  * inputs, as the Python package's autotuner does.
- *   dense_cols    shared-decay large-M engine: width in nodes of the tiles of
- *                 the dense dL/dalpha kernel: 64, 128 or 256 (128 needs
- *                 chunk_log2 <= 25 and 256 <= 24; otherwise the library's
- *                 rule applies)
- *   dense_ranges  the same kernel: event ranges per chunk, each with its own
+ *   dense_cols    shared-decay large-M engine: events (columns of the pair
+ *                 matrix) per block of the dense dL/dalpha kernels: 64, 128
+ *                 or 256
+ *   dense_ranges  the same kernels: event ranges per chunk, each with its own
  *                 partial sums: a power of two, 1..4096 (fewer if a chunk
  *                 has fewer segments)
  *   item_log2     small-M engine: log2 of the events per lane item, 4..16; a
  *                 value too small for the engine's bound on the item count
  *                 (and so on its workspace) is raised to the smallest that
  *                 fits
- *   dense_rows    the dense dL/dalpha kernel's tile height: 16 (float64
- *                 register accumulators) or 32 (float32 register
- *                 accumulators added to a float64 tile every few windows);
- *                 32 applies only with 256-column tiles and 128-record
- *                 windows (M > 128, chunk_log2 <= 24) */
+ *   dense_rows    16 or 32, accepted for callers that set it: the dense
+ *                 dL/dalpha tiles have 16 rows whatever it is */
 typedef struct hawkes_tuning {
     int32_t dense_cols;
     int32_t dense_ranges;
@@ -377,7 +375,7 @@ hawkes_status hawkes_check_inputs(const hawkes_problem* p,
  *   2 segment aggregates (large-M)       3 segment carry scan (large-M)
  *   4 per-item evaluation (small-M)      5 small-M aggregates and scans
  *   6 partition of a chunk's events by node block (large-M, gradient only)
- *   7 state checkpoints of the dense dL/dalpha (large-M, shared decay)
+ *   7 records and state rows of the dense dL/dalpha (large-M, shared decay)
  * Recording is host-side bookkeeping only (no device allocation); the events
  * are destroyed by hawkes_timing_read / hawkes_timing_reset.  Not for use
  * during graph capture.

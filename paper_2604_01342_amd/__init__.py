@@ -379,7 +379,7 @@ def simulate_n(mu, alpha, beta, n: int, seed: int):
 
 
 TIMING_KERNELS = {0: "dense_dalpha", 1: "forward", 2: "segment_aggregate", 3: "segment_scan",
-                  4: "small_compute", 5: "small_scan", 6: "bucket", 7: "dense_checkpoints"}
+                  4: "small_compute", 5: "small_scan", 6: "bucket", 7: "dense_prep"}
 
 
 def timing_enable(on: bool = True, kernels=None) -> None:

@@ -9,9 +9,8 @@ candidate is at least 1% faster), applies it with
 class, so that later processes skip the timing.
 
 Knobs (see include/hawkes.h):
-  dense_cols, dense_ranges,  the shared-decay large-M engine (M > 8): tile width
-  dense_rows                 and height of the dense dL/dalpha kernel and its
-                             event ranges
+  dense_cols, dense_ranges   the shared-decay large-M engine (M > 8): events per
+                             block and event ranges of the dense dL/dalpha
   item_log2                  the small-M engine (M <= 8, single or batched):
                              events per lane item
 
@@ -55,8 +54,9 @@ def _bucket(x: int) -> int:
 
 def shape_class_single(n: int, M: int, per_target: bool, chunk_log2: int) -> str:
     """Shapes that share a setting: M and n by powers of two, the decay mode,
-    the chunk size (it bounds the dense tile width)."""
-    return f"single|M{_bucket(M)}|n{_bucket(n)}|pt{int(per_target)}|ch{chunk_log2 or 20}"
+    the chunk size.  "blk": settings stored for the dense kernels before their
+    event blocks (tile widths) are not taken up."""
+    return f"single|M{_bucket(M)}|n{_bucket(n)}|pt{int(per_target)}|ch{chunk_log2 or 20}|blk"
 
 
 def shape_class_batched(S: int, n_total: int, max_m: int) -> str:
@@ -64,17 +64,11 @@ def shape_class_batched(S: int, n_total: int, max_m: int) -> str:
 
 
 def candidates_single(n: int, M: int, per_target: bool, chunk_log2: int) -> list[dict]:
-    lg = chunk_log2 or 20
     if per_target:
         return [{}]
     if M <= 8:
         return [{"item_log2": k} for k in range(4, 11)]
-    cols = [c for c in (64, 128, 256) if c <= max(64, 2 * M) and (c < 128 or lg <= (25 if c == 128 else 24))]
-    out = [{"dense_cols": c, "dense_ranges": r} for c in cols for r in (4, 8, 16, 32, 64)]
-    if 256 in cols and M > 128:
-        # 32-row tiles (float32 register accumulators) exist for 256 columns
-        out += [{"dense_cols": 256, "dense_ranges": r, "dense_rows": h} for r in (4, 8, 16, 32) for h in (16, 32)]
-    return out
+    return [{"dense_cols": c, "dense_ranges": r} for c in (64, 128, 256) for r in (2, 4, 8, 16, 32)]
 
 
 def candidates_batched(n_total: int) -> list[dict]:

@@ -187,24 +187,24 @@ __global__ __launch_bounds__(64 * HK_BSW) void bucket_scatter(int64_t c0, int64_
     }
 }
 
-// bs: log2 of the block width (4: 16 nodes, 6: 64, 7: 128; keys need
-// (events per chunk) << bs < 2^32); records go to the given arrays
-void bucket_chunk_into(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs,
-                       int32_t* cnt, int32_t* off, int32_t* base, uint32_t* key, double* tt, float* ww,
-                       hipStream_t st, bool counted) {
+void bucket_starts(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, int bs, int32_t* cnt, int32_t* off,
+                   hipStream_t st, bool counted) {
+    const int32_t nb = (A.M + (1 << bs) - 1) >> bs;
+    if (!counted)
+        hipLaunchKernelGGL(bucket_count, dim3(nseg), dim3(64), (size_t)nb * sizeof(int32_t), st, c0, c1, A.M, nb, bs,
+                           A.marks, nseg, cnt);
+    hipLaunchKernelGGL(bucket_scan, dim3(nb), dim3(1024), 0, st, nseg, cnt, off);
+}
+
+// bs: log2 of the block width (keys need (events per chunk) << bs < 2^32)
+void bucket_chunk(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs, hipStream_t st) {
     const int32_t nb = (A.M + (1 << bs) - 1) >> bs;
     int nbits = 0;
     while ((1 << nbits) < nb) ++nbits;
-    const size_t lds = (size_t)nb * sizeof(int32_t);
-    if (!counted)
-        hipLaunchKernelGGL(bucket_count, dim3(nseg), dim3(64), lds, st, c0, c1, A.M, nb, bs, A.marks, nseg, cnt);
-    hipLaunchKernelGGL(bucket_scan, dim3(nb), dim3(1024), 0, st, nseg, cnt, off);
-    hipLaunchKernelGGL(bucket_scatter, dim3(nseg), dim3(64 * HK_BSW), lds * (HK_BSW + 1), st, c0, c1, A.M, nb, nbits,
-                       bs, A.t, A.marks, wchunk, nseg, off, base, key, tt, ww);
-}
-
-void bucket_chunk(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs, hipStream_t st) {
-    bucket_chunk_into(A, c0, c1, nseg, wchunk, bs, A.bk_cnt, A.bk_off, A.bk_base, A.bk_key, A.bk_t, A.bk_w, st);
+    bucket_starts(A, c0, c1, nseg, bs, A.bk_cnt, A.bk_off, st, false);
+    hipLaunchKernelGGL(bucket_scatter, dim3(nseg), dim3(64 * HK_BSW), (size_t)nb * sizeof(int32_t) * (HK_BSW + 1), st,
+                       c0, c1, A.M, nb, nbits, bs, A.t, A.marks, wchunk, nseg, A.bk_off, A.bk_base, A.bk_key, A.bk_t,
+                       A.bk_w);
 }
 
 }  // namespace hk

@@ -9,22 +9,8 @@
 #endif
 #define HK_RB 64           // targets per block of the per-target (adjoint) dense kernel
 #define HK_SLAB 64         // columns per dense-gradient block (one per lane)
-#ifndef HK_DW
-#define HK_DW 2            // waves per workgroup of the shared-decay dense kernel
-#endif
-#ifndef HK_CKR
-#define HK_CKR 4           // segments per checkpoint run of the shared-decay dense gradient
-#endif
-#define HK_WIDE 60.0       // anchored-exponent limit inside one window of the dense kernel
-#ifndef HK_DWF
-#define HK_DWF 4           // waves per workgroup of the float32-accumulator dense kernel (32-row tiles)
-#endif
-#ifndef HK_F32_MIN_M
-#define HK_F32_MIN_M 384   // nodes from which the 32-row float32-accumulator tiles are the rule
-#endif
-// float64 words of a dense-gradient checkpoint slot: state, header, and
-// per record (64 NGW of them) its time, key and factor
-#define HK_SLOT_WORDS(CPL, NGW) (64 * (CPL) + 8 + 128 * (NGW))
+#define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32
+#define HK_WIDE 60.0       // anchored-exponent limit inside one block of the dense gradient
 
 namespace hk {
 
@@ -41,13 +27,14 @@ struct LargeArgs {
     int32_t nseg;         // segments per chunk
     int32_t ER;           // event ranges of the dense kernel per chunk
     int32_t NB;           // node blocks of 64 (bucketing; columns of the dense kernels)
-    int32_t NBR;          // row blocks of the dense kernel (DR rows shared decay, HK_RB per target)
-    int32_t CPL;          // columns per lane of the shared-decay dense kernel (1, 2, 4 or 8)
-    int32_t DRB;          // log2 of DR, the rows per block of the shared-decay dense kernel
-    int32_t NGW;          // groups of 64 column records per window of the shared-decay dense kernel (1, 2)
-    int32_t NBC;          // column blocks of the dense kernel (64 CPL columns each)
-    int32_t CKR;          // segments per checkpoint run (shared decay)
-    int32_t NRUN;         // checkpoint runs per chunk (nseg / CKR)
+    int32_t NBR, NBC;     // row and column blocks of the per-target dense kernel
+    // shared decay (hk_dense.hip)
+    int32_t BL;           // log2 of the events per block (6, 7 or 8)
+    int32_t DRB;          // log2 of the rows per tile (4)
+    int32_t CW, NCB;      // columns per tile (a multiple of 16), column blocks
+    int32_t NSP;          // rows of spart and cpart_
+    bool row64;           // rows of U and K in float64
+    int32_t Mp;           // row length of urow and krow: M, padded to 64
     bool grad;
     bool support;         // dL/dalpha only at alpha's nonzeros (zero elsewhere), shared decay
     const double* t;
@@ -74,14 +61,15 @@ struct LargeArgs {
     double* acc;          // [2 + 2K] call-level sums: logsum, comp, E[K], gbeta[K]
     double* ll_scratch;   // [1] log-likelihood slot when the caller wants intensities only
     bool carry_prefix;    // carry_seg holds in-group prefixes (the scan's apply pass left out)
-    double *gpart, *spart, *cpart_;  // [ER][M][M]; [ER][M] per target, [NRUN][M] shared decay
+    double *gpart, *spart, *cpart_;  // [ER][M][M]; [ER][M] (sums of w, of compensator terms or event counts)
     double* csum;         // [M] the columns' compensator sums (shared decay, gradient)
     double* gsup;         // [min(8, ER)][M*M] support-restricted first term of eq. 9 in CSR order (the
                           //   first nnz(alpha) entries of each copy; shares gpart's space)
-    int64_t nslot;        // checkpoint slots
-    double* kck;          // [nslot][HK_SLOT_WORDS(CPL, NGW)] state checkpoints of the dense gradient (shared
-                          //   decay) with their groups' records
-    int4* runinfo;        // [NBC][NRUN] per checkpoint run: first slot, groups, P0, P1
+    // dense gradient, shared decay: rows of U and K per block of events, pair
+    // records per event (block order), and whether a block is wide
+    double *urow, *krow;  // [CH >> BL][Mp] (and slack for a column block past the row); float32 unless row64
+    uint2* prec;          // [CH] place in the block << 16 | 8 mark (place 0xffff: none), e^{beta (t_j - tau_b)}
+    int32_t* wide;        // [CH >> BL]
     // per-target decays (R-form forward, reverse adjoint for the gradient)
     int32_t* csc_ptr;   // alpha by column: targets p of source q
     int2* csc_cv;       // (target, float bits of the value)
@@ -104,13 +92,13 @@ struct LargeArgs {
     double* bk_t;         // [CH] event time
     float* bk_w;          // [CH] 1 / lambda
     float* wchunk;        // [CH] 1 / lambda of the chunk's events (shared decay)
-    // the same events partitioned by blocks of DR nodes (the row blocks of
-    // the shared-decay dense kernel): its own-event streams
-    int32_t NBO;          // row blocks (ceil(M / DR))
+    // the events partitioned by blocks of 2^DRB nodes: the pair kernel's own
+    // events
+    int32_t NBO;          // row blocks (ceil(M / 2^DRB))
     int32_t *bo_cnt, *bo_off, *bo_base;
-    uint32_t* bo_key;     // [CH] (index in chunk) << DRB | mark mod DR
-    double* bo_t;
-    float* bo_w;
+    uint32_t* bo_key;     // [CH] (index in chunk) << DRB | mark mod 2^DRB
+    float2* bo_cw;        // [CH] (beta w e^{-beta (t - tau_b)}, w)
+    double* bo_e;         // [CH] 1 - e^{-beta (T - t)}
     // outputs
     double *loglik, *g_mu, *g_alpha, *g_beta;
     float* lambda_out;
@@ -137,7 +125,7 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st);
 // helpers shared by the two large-M paths (host side)
 size_t lds_limit();
 hawkes_status allow_lds(const void* kernel, size_t bytes, bool with_static = false);
-// grants the float32-accumulator dense kernel its LDS tile (when the layout selects it)
+// grants the shared-decay dense kernels their LDS
 hawkes_status dense_allow_lds(const LargeArgs& A);
 void large_build_index(int32_t M, const float* alpha, int trans, int32_t* ptr, int2* cv, hipStream_t st);
 // entries between consecutive kernels' packed rows of alpha: even (each
@@ -149,13 +137,15 @@ inline int64_t cv_stride(int64_t MM) { return (MM + 2) & ~(int64_t)1; }
 void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st, bool apply = true);
 void large_chunk_acc_launch(int32_t nseg, int32_t width, const double* seg_part, double* acc, hipStream_t st);
 void bucket_chunk(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs, hipStream_t st);
-// counted: cnt already holds the counts (the forward pass made them)
-void bucket_chunk_into(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs,
-                       int32_t* cnt, int32_t* off, int32_t* base, uint32_t* key, double* tt, float* ww,
-                       hipStream_t st, bool counted = false);
-// ck_only: the checkpoint kernel alone (its per-column sums of dL/dmu and
-// the compensator), for the support-restricted gradient
-void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipStream_t st, bool ck_only);
+// starts of the (node block, segment) runs alone; counted: cnt already holds
+// the counts (the forward pass made them)
+void bucket_starts(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, int bs, int32_t* cnt, int32_t* off,
+                   hipStream_t st, bool counted);
+// first: the chunk's results replace the partials (the call's first chunk);
+// sums_only: the sums per node alone (dL/dmu and the compensator), for the
+// support-restricted gradient
+void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipStream_t st, bool first,
+                        bool sums_only);
 
 // final sums and outputs of kernel k (see large_final); csum: the columns' compensator sums, or null
 void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,

@@ -24,11 +24,11 @@
 //            plus the same-batch events found through a per-node lane mask.
 //            It writes lambda_i / per-segment float64 partials and, for the
 //            gradient, per-event coefficients for the dense kernel.
-//   bucket   the chunk's events partitioned by blocks of 16 nodes (hk_bucket.hip)
-//   dense    dense dL/dalpha (first term of eq. 9, hk_dense.hip): state
-//            checkpoints per column block, then tiles of 16 rows x up to 256
-//            columns per event range, the rank-1 part of each window in
-//            registers and its pair terms in float64 LDS.
+//   bucket   the starts of the partition of the chunk's events by blocks of 16
+//            nodes (hk_bucket.hip)
+//   dense    dense dL/dalpha (first term of eq. 9, hk_dense.hip): per block of
+//            events the state's rows and the events' records, then tiles of 16
+//            rows per event range, pair terms and matrix product side by side
 #include "hk_device.h"
 #include "hk_large.h"
 #include <stdlib.h>
@@ -967,66 +967,53 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     A.nchunks = (A.n + A.CH - 1) / A.CH;
     A.nseg = (int32_t)((A.CH + HK_SEG - 1) / HK_SEG);
     A.NB = (A.M + 63) / 64;
-    // shared decay: tiles of DR = 16 rows x W = 64 CPL columns.  Every own
-    // event is visited once per column block (a pair-term instruction each),
-    // every window once per row block (state loads and the rank-1 update),
-    // and G takes 16 CPL float64 registers per lane: 16 x 256 is the fastest
-    // that fits (two waves per SIMD), with 16 x 128 and 16 x 64 for the
-    // longer chunks, since a column record key holds the event index above
-    // log2(W) bits, and no wider than the nodes need.  A tuned width
-    // (hawkes_set_tuning) replaces the rule where the chunk allows it.
     const hawkes_tuning tu = tuning_snapshot();
-    A.CPL = A.per_target ? 1 : lg <= 24 ? 4 : lg <= 25 ? 2 : 1;
-    while (A.CPL > 1 && 32 * A.CPL >= A.M) A.CPL >>= 1;
-    if (!A.per_target && tu.dense_cols > 0) {
-        const int v = tu.dense_cols / 64;
-        const int vlg = v == 4 ? 24 : v == 2 ? 25 : 26;
-        if (lg <= vlg) A.CPL = v;
+    A.NBR = A.NBC = A.NB;
+    if (A.per_target) {
+        // event ranges per chunk for the per-target dense kernel: a power of
+        // two so that the ranges map onto the 8 XCDs evenly, about 2048
+        // workgroups in total
+        const int64_t want = (2048 + (int64_t)A.NB * A.NB - 1) / ((int64_t)A.NB * A.NB);
+        int32_t er = 1;
+        while (er < want) er <<= 1;
+        while (er > A.nseg && er > 1) er >>= 1;
+        A.ER = er;
+        A.DRB = 6;
+        A.BL = 6;
+    } else {
+        // dense dL/dalpha (hk_dense.hip).  Events per block: the pair terms
+        // cost half a block of records per event, the rank-one product M^2
+        // multiply-adds per block.  dense_prep + dense_tiles, us a launch with
+        // 64 / 128 / 256 events: M = 50, n = 1e6: 119 / 142 / 208; M = 251,
+        // n = 3e5: 54 / 49 / 58; M = 700, 2^20: - / 223 / 203; M = 1000,
+        // 2^20: - / 335 / 215 (an earlier form)
+        A.BL = A.M > 512 ? 8 : A.M > 128 ? 7 : 6;
+        if (tu.dense_cols > 0) A.BL = tu.dense_cols == 256 ? 8 : tu.dense_cols == 128 ? 7 : 6;
+        // tiles of 16 rows x up to 1024 columns (128 KiB of LDS): one column
+        // block, or several of a multiple of 64 columns
+        A.NCB = (A.M + 1023) / 1024;
+        A.CW = A.NCB == 1 ? (A.M + 15) & ~15 : (((A.M + A.NCB - 1) / A.NCB) + 63) & ~63;
+        A.DRB = 4;
+        A.NBO = (A.M + 15) >> 4;
+        // event ranges: one round of workgroups (one a CU), and at least two
+        // blocks for every wave
+        const int64_t blks = ((A.n < A.CH ? A.n : A.CH) >> A.BL) + 1;
+        int64_t er = 256 / ((int64_t)A.NBO * A.NCB);
+        if (er > blks / 24) er = blks / 24;
+        // and about 32 MiB of partials
+        const int64_t most = ((int64_t)32 << 20) / ((int64_t)A.K * A.M * A.M * 8);
+        if (er > 4 && er > most) er = most > 4 ? most : 4;
+        if (tu.dense_ranges > 0) {
+            er = tu.dense_ranges;
+            while (er > A.nseg) er >>= 1;
+        }
+        A.ER = er < 1 ? 1 : (int32_t)er;
     }
-    A.DRB = 4;
-    // window length of the dense kernel: a 64-record window holds about
-    // 1024 / max(W, M) own events of a 16-row block; with fewer than 8 the
-    // rank-1 update's u is mostly zero, and 128-record windows halve the
-    // per-window work at about 1.5 pair instructions per own event
-    {
-        const int Wc = 64 * A.CPL;
-        A.NGW = !A.per_target && 1024 / (Wc > A.M ? Wc : A.M) < 8 ? 2 : 1;
-    }
-    // 32-row tiles with float32 register accumulators (large_dense_f) for the
-    // widest tiles at large M: half the window visits per event; the tuning
-    // (dense_rows) can select either where the tiles are 256 x 128-record
-    if (!A.per_target && A.CPL == 4 && A.NGW == 2) {
-        if (tu.dense_rows == 32 || (tu.dense_rows == 0 && A.M >= HK_F32_MIN_M)) A.DRB = 5;
-    }
-    const int nwv = A.DRB == 5 ? HK_DWF : HK_DW;   // waves per dense workgroup
-    A.NBR = A.per_target ? A.NB : (A.M + (1 << A.DRB) - 1) >> A.DRB;
-    A.NBC = A.per_target ? A.NB : (A.M + 64 * A.CPL - 1) / (64 * A.CPL);
-    // event ranges per chunk for the dense kernel: a power of two so that the
-    // ranges map onto the 8 XCDs evenly; about 4096 workgroups in total
-    // (shared decay: two waves each, 18 KiB of LDS per group, so that several
-    // rounds balance the waves' uneven work) or 2048 (per target, 34 KiB;
-    // 16 x 256 tiles, 34 KiB and two waves per SIMD: measured best at c4's
-    // size) unless the tuning (hawkes_set_tuning) sets it
-    // (32-row float32-accumulator tiles: 512 workgroups of four waves, two
-    // resident per CU, i.e. one round; measured at c4, dense ms per launch
-    // with 4 / 8 / 16 / 32 ranges: 0.416 / 0.420 / 0.434 / 0.534, and a
-    // quarter of the partials' traffic at 4)
-    const int64_t nbb = (int64_t)A.NBR * A.NBC;
-    const int64_t target = A.DRB == 5 ? 2048 / HK_DWF : A.per_target || A.CPL == 4 ? 2048 : 4096;
-    const int64_t want = (target + nbb - 1) / nbb;
-    int32_t er = 1;
-    while (er < want) er <<= 1;
-    if (!A.per_target && tu.dense_ranges > 0) er = tu.dense_ranges;   // a knob of the shared-decay kernel only
-    while (er > A.nseg && er > 1) er >>= 1;
-    // shared decay: every wave of a dense workgroup gets at least one run
-    while (!A.per_target && er > 1 && A.nseg / er < nwv) er >>= 1;
-    A.ER = er;
-    // checkpoint runs: whole runs per event range, nwv or more per range
-    // (nseg and ER are powers of two)
-    A.CKR = A.nseg / (er * nwv);
-    if (A.CKR > HK_CKR) A.CKR = HK_CKR;
-    if (A.CKR < 1) A.CKR = 1;
-    A.NRUN = A.nseg / A.CKR;
+    // rows of the sums per node: one a range; of one size for up to 16 ranges
+    // where they are small beside the dL/dalpha partials
+    A.NSP = A.ER < 16 && !A.per_target && A.K == 1 && A.NCB == 1 ? 16 : A.ER;
+    A.Mp = (A.M + 63) & ~63;
+    A.row64 = A.M < HK_F32_MIN_M;
     A.grad = grad;
     const int64_t M = A.M, MM = M * M, K = A.K;
     Carve c(ws, ws_bytes);
@@ -1086,20 +1073,20 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
             A.bk_w = c.take<float>(A.CH);
         }
         A.gpart = c.take<double>((size_t)K * A.ER * MM);
-        const int64_t nsp = A.per_target ? A.ER : A.NRUN;
-        A.spart = c.take<double>((size_t)K * nsp * M);
-        A.cpart_ = c.take<double>((size_t)K * nsp * M);
+        A.spart = c.take<double>((size_t)K * A.NSP * M);
+        A.cpart_ = c.take<double>((size_t)K * A.NSP * M);
         if (!A.per_target) {
-            A.nslot = A.CH / (64 * A.NGW) + 2 * (int64_t)A.NBC * A.NRUN + 2;
-            A.kck = c.take<double>((size_t)A.nslot * HK_SLOT_WORDS(A.CPL, A.NGW));
-            A.runinfo = c.take<int4>((size_t)A.NBC * A.NRUN);
-            A.NBO = (A.M + (1 << A.DRB) - 1) >> A.DRB;
+            const size_t rows = (size_t)(A.CH >> A.BL) * A.Mp + 1024;
+            A.urow = c.take<double>(A.row64 ? rows : rows / 2);
+            A.krow = c.take<double>(A.row64 ? rows : rows / 2);
+            A.prec = c.take<uint2>(A.CH);
+            A.wide = c.take<int32_t>(A.CH >> A.BL);
             A.bo_cnt = c.take<int32_t>((size_t)A.NBO * A.nseg);
             A.bo_off = c.take<int32_t>((size_t)A.NBO * (A.nseg + 1));
             A.bo_base = c.take<int32_t>(A.NBO);
             A.bo_key = c.take<uint32_t>(A.CH);
-            A.bo_t = c.take<double>(A.CH);
-            A.bo_w = c.take<float>(A.CH);
+            A.bo_cw = c.take<float2>(A.CH);
+            A.bo_e = c.take<double>(A.CH);
         }
     }
     return c.off + 256;
@@ -1189,6 +1176,19 @@ void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st
 // lambda and the shared w_i = 1/lambda_i; with the gradient the chunk's events
 // are partitioned once and the dense dL/dalpha kernels run once per kernel
 // (decay beta_k, kernel k's state checkpoints and partial sums).
+static void fill_launch(double* p, int64_t n, hipStream_t st) {
+    const int64_t nb = (n + 255) / 256;
+    hipLaunchKernelGGL(fill_d, dim3((unsigned)(nb < 65535 ? nb : 65535)), dim3(256), 0, st, p, n, 0.0);
+}
+
+// the dense gradient's partials of a sequence without events (otherwise the
+// first chunk stores them)
+static void dense_zero(const LargeArgs& A, hipStream_t st) {
+    fill_launch(A.gpart, (int64_t)A.K * A.ER * A.M * A.M, st);
+    fill_launch(A.spart, (int64_t)A.K * A.NSP * A.M, st);
+    fill_launch(A.cpart_, (int64_t)A.K * A.NSP * A.M, st);
+}
+
 static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
     const int32_t M = A.M, K = A.K;
     const int64_t MM = (int64_t)M * M;
@@ -1199,19 +1199,11 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
         allow_lds((const void*)large_forward<true, false, false, HK_FWW, true>, lds_fwd) != HAWKES_OK ||
         allow_lds((const void*)large_forward<false, false, false, HK_FWW, true>, lds_fwd) != HAWKES_OK)
         return HAWKES_EUNSUPPORTED;
-    if (A.grad && (uint64_t)A.nslot * (uint64_t)HK_SLOT_WORDS(A.CPL, A.NGW) * 8u >= (1ull << 32))
-        return HAWKES_EUNSUPPORTED;
     if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const int32_t W = 2 + 2 * K;
     hipLaunchKernelGGL(fill_d, dim3(16), dim3(256), 0, st, A.carry, (int64_t)K * 2 * M, 0.0);
     hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)W, 0.0);
-    if (A.grad) {
-        const int64_t ng = (int64_t)K * A.ER * MM;
-        hipLaunchKernelGGL(fill_d, dim3((unsigned)((ng + 255) / 256 < 65535 ? (ng + 255) / 256 : 65535)),
-                           dim3(256), 0, st, A.gpart, ng, 0.0);
-        hipLaunchKernelGGL(fill_d, dim3(64), dim3(256), 0, st, A.spart, (int64_t)K * A.NRUN * M, 0.0);
-        hipLaunchKernelGGL(fill_d, dim3(64), dim3(256), 0, st, A.cpart_, (int64_t)K * A.NRUN * M, 0.0);
-    }
+    if (A.grad && A.nchunks == 0) dense_zero(A, st);
     // per kernel: column sums, CSR copy and node records of alpha^k
     for (int32_t k = 0; k < K; ++k) {
         const float* ak = A.alpha + (int64_t)k * MM;
@@ -1230,8 +1222,8 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
         B.carry = A.carry + (int64_t)k * 2 * M;
         B.carry_seg = A.carry_seg + (int64_t)k * A.nseg * 2 * M;
         B.gpart = A.gpart ? A.gpart + (int64_t)k * A.ER * MM : nullptr;
-        B.spart = A.spart ? A.spart + (int64_t)k * A.NRUN * M : nullptr;
-        B.cpart_ = A.cpart_ ? A.cpart_ + (int64_t)k * A.NRUN * M : nullptr;
+        B.spart = A.spart ? A.spart + (int64_t)k * A.NSP * M : nullptr;
+        B.cpart_ = A.cpart_ ? A.cpart_ + (int64_t)k * A.NSP * M : nullptr;
         return B;
     };
     for (int64_t ch = 0; ch < A.nchunks; ++ch) {
@@ -1286,19 +1278,18 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
         if (A.grad) {
             {
                 TimedScope tb(6, st);
-                bucket_chunk_into(A, c0, c1, nseg, A.wchunk, A.DRB, A.bo_cnt, A.bo_off, A.bo_base, A.bo_key, A.bo_t,
-                                  A.bo_w, st, false);
+                bucket_starts(A, c0, c1, nseg, A.DRB, A.bo_cnt, A.bo_off, st, false);
             }
             for (int32_t k = 0; k < K; ++k) {
                 LargeArgs B = view(k);
-                large_dense_launch(B, c0, c1, nseg, st, false);
+                large_dense_launch(B, c0, c1, nseg, st, ch == 0, false);
             }
         }
     }
     for (int32_t k = 0; k < K; ++k) {
         LargeArgs B = view(k);
         B.K = K;
-        large_final_launch(B, A.NRUN, nullptr, B.gpart, B.spart, B.cpart_, A.g_alpha ? A.g_alpha + k * MM : nullptr,
+        large_final_launch(B, A.ER, nullptr, B.gpart, B.spart, B.cpart_, A.g_alpha ? A.g_alpha + k * MM : nullptr,
                            nullptr, k, st);
         if (!A.grad) break;   // the log-likelihood needs one launch
     }
@@ -1319,16 +1310,12 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
         allow_lds((const void*)large_forward<false, true, false, HK_FWW>, lds_fwd) != HAWKES_OK ||
         allow_lds((const void*)large_forward<false, false, false, HK_FWW>, lds_fwd) != HAWKES_OK)
         return HAWKES_EUNSUPPORTED;
-    if (A.grad && !A.support && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
+    if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const bool sup = A.grad && A.support;
     // support-restricted: the first term's copies (CSR order) take the place
-    // of the dense partials, min(8, ER) of them (ER is a power of two)
-    const int32_t ncopy = A.ER < 8 ? A.ER : 8;
+    // of the dense partials, up to 8 of them (a power of two)
+    const int32_t ncopy = A.ER >= 8 ? 8 : A.ER >= 4 ? 4 : A.ER >= 2 ? 2 : 1;
     if (sup) A.gsup = A.gpart;
-    // the dense-gradient kernels address checkpoints and records with
-    // 32-bit byte offsets
-    if (A.grad && (uint64_t)A.nslot * (uint64_t)HK_SLOT_WORDS(A.CPL, A.NGW) * 8u >= (1ull << 32))
-        return HAWKES_EUNSUPPORTED;
     // zero the carried state and accumulators
     hipLaunchKernelGGL(fill_d, dim3(1), dim3(256), 0, st, A.carry, (int64_t)2 * M, 0.0);
     hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)4, 0.0);
@@ -1358,14 +1345,8 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
         }
     }
     A.carry_prefix = true;
-    if (A.grad) {
-        // the dense partials, or (support-restricted) the CSR-ordered sums
-        const int64_t ng = (sup ? ncopy : A.ER) * MM;
-        hipLaunchKernelGGL(fill_d, dim3((unsigned)((ng + 255) / 256 < 65535 ? (ng + 255) / 256 : 65535)),
-                           dim3(256), 0, st, sup ? A.gsup : A.gpart, ng, 0.0);
-        hipLaunchKernelGGL(fill_d, dim3(64), dim3(256), 0, st, A.spart, (int64_t)A.NRUN * M, 0.0);
-        hipLaunchKernelGGL(fill_d, dim3(64), dim3(256), 0, st, A.cpart_, (int64_t)A.NRUN * M, 0.0);
-    }
+    if (A.grad && A.nchunks == 0) dense_zero(A, st);
+    if (sup) fill_launch(A.gsup, ncopy * MM, st);   // the CSR-ordered sums
     hipLaunchKernelGGL(large_colsum, dim3((unsigned)((M + 63) / 64)), dim3(1024), 0, st, M, A.alpha, A.colsum);
     large_build_index(M, A.alpha, 0, A.csr_ptr, A.csr_cv, st);
     hipLaunchKernelGGL(large_node_info, dim3(gM), dim3(256), 0, st, M, A.csr_ptr, A.mu, A.colsum, A.node_info);
@@ -1411,16 +1392,15 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
         if (A.grad) {
             {
                 TimedScope tb(6, st);
-                bucket_chunk_into(A, c0, c1, nseg, A.wchunk, A.DRB, A.bo_cnt, A.bo_off, A.bo_base, A.bo_key, A.bo_t,
-                                  A.bo_w, st, X.bcnt != nullptr);
+                bucket_starts(A, c0, c1, nseg, A.DRB, A.bo_cnt, A.bo_off, st, X.bcnt != nullptr);
             }
-            // support-restricted: only the checkpoint kernel's per-column
-            // sums (dL/dmu, compensator) are needed
-            large_dense_launch(A, c0, c1, nseg, st, sup);
+            // support-restricted: only the sums per node (dL/dmu,
+            // compensator) are needed
+            large_dense_launch(A, c0, c1, nseg, st, ch == 0, sup);
         }
     }
     hipLaunchKernelGGL(large_chunk_acc, dim3(1), dim3(256), 0, st, A.nseg, 4, A.seg_part, A.acc);
-    large_final_launch(A, A.NRUN, nullptr, sup ? nullptr : A.gpart, A.spart, A.cpart_, A.g_alpha, A.csum, 0, st);
+    large_final_launch(A, A.ER, nullptr, sup ? nullptr : A.gpart, A.spart, A.cpart_, A.g_alpha, A.csum, 0, st);
     if (sup && A.g_alpha)
         hipLaunchKernelGGL(large_sup_scatter, dim3((unsigned)M), dim3(64), 0, st, M, ncopy, A.csr_ptr, A.csr_cv,
                            A.gsup, A.csum, A.g_alpha);
