@@ -229,8 +229,8 @@ static hawkes_status run_single(const hawkes_problem* p, const double* t, const 
     A.g_mu = g_mu; A.g_alpha = g_alpha; A.g_beta = g_beta;
     A.lambda_out = lambda_out;
     // one shared decay: the first term only on the support (forward pass);
-    // per target or several kernels: the dense gradient, masked
-    A.support = support && !A.per_target && A.K == 1;
+    // few nodes, per target or several kernels: the dense gradient, masked
+    A.support = support && !A.per_target && A.K == 1 && !A.narrow;
     const hawkes_status st = run_large(A, stream);
     return st == HAWKES_OK && support && !A.support ? mask_support(p, alpha, g_alpha, stream) : st;
 }

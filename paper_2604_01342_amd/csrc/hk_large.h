@@ -9,6 +9,7 @@
 #endif
 #define HK_RB 64           // targets per block of the per-target (adjoint) dense kernel
 #define HK_SLAB 64         // columns per dense-gradient block (one per lane)
+#define HK_NARROW_MAX_M 64   // nodes up to which one kernel takes the forward pass and the gradient
 #define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32
 #define HK_WIDE 60.0       // anchored-exponent limit inside one block of the dense gradient
 
@@ -28,7 +29,8 @@ struct LargeArgs {
     int32_t ER;           // event ranges of the dense kernel per chunk
     int32_t NB;           // node blocks of 64 (bucketing; columns of the dense kernels)
     int32_t NBR, NBC;     // row and column blocks of the per-target dense kernel
-    // shared decay (hk_dense.hip)
+    // shared decay: one kernel for few nodes (hk_narrow.hip), else hk_dense.hip
+    bool narrow;
     int32_t BL;           // log2 of the events per block (6, 7 or 8)
     int32_t DRB;          // log2 of the rows per tile (4)
     int32_t CW, NCB;      // columns per tile (a multiple of 16), column blocks
@@ -151,6 +153,9 @@ void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipS
 void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,
                         const double* spart, const double* cpart, double* g_alpha, double* csum, int32_t k,
                         hipStream_t st);
+
+// the chunk's forward pass and gradient for up to HK_NARROW_MAX_M nodes
+hawkes_status narrow_launch(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, bool first, hipStream_t st);
 
 size_t seq_workspace_bytes(const hawkes_problem* p);
 hawkes_status run_sequential(const hawkes_problem* p, const double* t, const int32_t* marks, const float* mu,

@@ -829,12 +829,11 @@ __global__ __launch_bounds__(256) void large_combine(int64_t c0, int64_t c1, int
 // gbeta[K]); ebacc: per-target decays, dL/dbeta = -ebacc, else null.
 // Every entry is summed over ER partials of dL/dalpha, and its column over NSC
 // partials of the weights and compensator terms, each in a fixed order: a
-// workgroup takes 16 columns and FIN_ROWS rows, its 16 thread rows are ES
+// workgroup takes 16 columns and FR rows, its 16 thread rows are ES
 // slices of the partials times 16 / ES matrix rows, slice sums are added by a
 // tree.  Bound by the read of the partials; with one thread per entry the 512
 // partials of a 16-node model were a chain of dependent loads (n = 1e6:
 // 123 us, and 35 us more for the column sums, against 10 us now).
-#define FIN_ROWS 16
 __device__ __forceinline__ double fin_tree(double v, double (*sh)[17], int c, int s, int w) {
     // sum of v over the w slices of this thread's group (w a power of two,
     // groups of w consecutive s), returned to the group's first slice
@@ -856,7 +855,7 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
                                                    const double* __restrict__ cpart, double* __restrict__ loglik,
                                                    double* __restrict__ g_mu, double* __restrict__ g_alpha,
                                                    double* __restrict__ g_beta, double* __restrict__ csum, int grad,
-                                                   int32_t K, int32_t k) {
+                                                   int32_t K, int32_t k, int32_t FR) {
     __shared__ double sh[16][17];
     __shared__ double ps[256];
     const int64_t MM = (int64_t)M * M;
@@ -882,7 +881,7 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
     // the columns' compensator sums (every workgroup of the columns), dL/dmu
     // and the per-target dL/dbeta (the first)
     double cs = 0.0;
-#pragma unroll 4
+#pragma unroll 8
     for (int32_t e = s; e < NSC; e += 16) cs += cpart[(int64_t)e * M + qc];
     cs = fin_tree(cs, sh, c, s, 16);
     if (s == 0) ps[c] = cs;
@@ -891,7 +890,7 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
     if (blockIdx.y == 0) {
         if (k == 0) {
             double v = 0.0;
-#pragma unroll 4
+#pragma unroll 8
             for (int32_t e = s; e < NSC; e += 16) v += spart[(int64_t)e * M + qc];
             v = fin_tree(v, sh, c, s, 16);
             if (s == 0 && q < M && g_mu) g_mu[q] = v - T;
@@ -903,13 +902,13 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
     }
     if (!g_alpha) return;
     const int rw = 16 / ES, es = s & (ES - 1);
-    for (int32_t r0 = 0; r0 < FIN_ROWS; r0 += rw) {
-        const int32_t row = blockIdx.y * FIN_ROWS + r0 + s / ES;
+    for (int32_t r0 = 0; r0 < FR; r0 += rw) {
+        const int32_t row = blockIdx.y * FR + r0 + s / ES;
         const int32_t rc = row < M ? row : M - 1;
         const int64_t x = (int64_t)rc * M + qc;
         double g = 0.0;
         if (gpart) {
-#pragma unroll 4
+#pragma unroll 8
             for (int32_t e = es; e < ER; e += ES) g += gpart[(int64_t)e * MM + x];
         }
         if (ES > 1) g = fin_tree(g, sh, c, s, ES);
@@ -921,14 +920,18 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
 void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,
                         const double* spart, const double* cpart, double* g_alpha, double* csum, int32_t k,
                         hipStream_t st) {
-    const unsigned gx = (unsigned)((A.M + 15) / 16), gy = (unsigned)((A.M + FIN_ROWS - 1) / FIN_ROWS);
     // slices of the partials: enough that a slice sums at most about 8, as
     // long as that leaves a slice several
     int32_t ES = 1;
     while (ES < 16 && A.ER > 8 * ES) ES <<= 1;
+    // rows per workgroup: 16, or one pass of its thread rows where that leaves
+    // the chip idle (few nodes)
+    const unsigned gx = (unsigned)((A.M + 15) / 16);
+    const int32_t FR = (int64_t)gx * gx < 256 ? 16 / ES : 16;
+    const unsigned gy = (unsigned)((A.M + FR - 1) / FR);
     hipLaunchKernelGGL(large_final, A.grad ? dim3(gx, g_alpha ? gy : 1) : dim3(1), dim3(256), 0, st, A.M, A.ER, NSC,
                        ES, A.T, A.mu, A.acc, ebacc, gpart, spart, cpart, A.loglik, A.g_mu, g_alpha, A.g_beta, csum,
-                       A.grad ? 1 : 0, A.K, k);
+                       A.grad ? 1 : 0, A.K, k, FR);
 }
 
 // support-restricted dL/dalpha: one wave per row p writes, for each nonzero
@@ -969,7 +972,21 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     A.NB = (A.M + 63) / 64;
     const hawkes_tuning tu = tuning_snapshot();
     A.NBR = A.NBC = A.NB;
-    if (A.per_target) {
+    // few nodes, one kernel: hk_narrow.hip, up to the 64 lanes of a wave.  The
+    // forward pass, partition and dense kernels against it, n = 1e6: M = 16:
+    // 87 + 14 + 86 us against 44; M = 50, dense rows: 119 + 13 + 119 against 95
+    A.narrow = !A.per_target && A.K == 1 && A.M <= HK_NARROW_MAX_M;
+    if (A.narrow) {
+        // workgroups (each with its partial sums), two segments a round: two
+        // a CU where the sequence has that many
+        const int64_t segs = A.n < A.CH ? (A.n + HK_SEG - 1) / HK_SEG : A.nseg;
+        int64_t er = (segs + 1) / 2 < 512 ? (segs + 1) / 2 : 512;
+        if (tu.dense_ranges > 0) {
+            er = tu.dense_ranges;
+            while (er > A.nseg) er >>= 1;
+        }
+        A.ER = er < 1 ? 1 : (int32_t)er;
+    } else if (A.per_target) {
         // event ranges per chunk for the per-target dense kernel: a power of
         // two so that the ranges map onto the 8 XCDs evenly, about 2048
         // workgroups in total
@@ -1011,7 +1028,7 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     }
     // rows of the sums per node: one a range; of one size for up to 16 ranges
     // where they are small beside the dL/dalpha partials
-    A.NSP = A.ER < 16 && !A.per_target && A.K == 1 && A.NCB == 1 ? 16 : A.ER;
+    A.NSP = A.ER < 16 && !A.per_target && !A.narrow && A.K == 1 && A.NCB == 1 ? 16 : A.ER;
     A.Mp = (A.M + 63) & ~63;
     A.row64 = A.M < HK_F32_MIN_M;
     A.grad = grad;
@@ -1063,7 +1080,7 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         }
     }
     if (grad) {
-        if (!A.per_target) A.wchunk = c.take<float>(A.CH);
+        if (!A.per_target && !A.narrow) A.wchunk = c.take<float>(A.CH);
         if (A.per_target) {
             A.bk_cnt = c.take<int32_t>((size_t)A.NB * A.nseg);
             A.bk_off = c.take<int32_t>((size_t)A.NB * (A.nseg + 1));
@@ -1075,7 +1092,7 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         A.gpart = c.take<double>((size_t)K * A.ER * MM);
         A.spart = c.take<double>((size_t)K * A.NSP * M);
         A.cpart_ = c.take<double>((size_t)K * A.NSP * M);
-        if (!A.per_target) {
+        if (!A.per_target && !A.narrow) {
             const size_t rows = (size_t)(A.CH >> A.BL) * A.Mp + 1024;
             A.urow = c.take<double>(A.row64 ? rows : rows / 2);
             A.krow = c.take<double>(A.row64 ? rows : rows / 2);
@@ -1296,9 +1313,41 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
+// one sequence of up to HK_NARROW_MAX_M nodes: segment maps and their scan, then
+// one kernel per chunk
+static hawkes_status run_narrow(LargeArgs& A, hipStream_t st) {
+    const int32_t M = A.M;
+    hipLaunchKernelGGL(fill_d, dim3(1), dim3(256), 0, st, A.carry, (int64_t)2 * M, 0.0);
+    hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)4, 0.0);
+    hipLaunchKernelGGL(fill_d, dim3(4), dim3(256), 0, st, A.seg_part, (int64_t)A.nseg * 4, 0.0);
+    if (A.grad && A.nchunks == 0) dense_zero(A, st);
+    hipLaunchKernelGGL(large_colsum, dim3((unsigned)((M + 63) / 64)), dim3(1024), 0, st, M, A.alpha, A.colsum);
+    for (int64_t ch = 0; ch < A.nchunks; ++ch) {
+        const int64_t c0 = ch * A.CH;
+        const int64_t c1 = c0 + A.CH < A.n ? c0 + A.CH : A.n;
+        const int32_t nseg = (int32_t)((c1 - c0 + HK_SEG - 1) / HK_SEG);
+        {
+            TimedScope ts(2, st);
+            hipLaunchKernelGGL(large_seg_agg, dim3(nseg), dim3(64), (size_t)2 * M * sizeof(double), st, c0, c1, M,
+                               A.t, A.marks, A.beta, A.agg, A.seg_span, A.seg_dec);
+        }
+        {
+            TimedScope ts(3, st);
+            large_scan(A, nseg, nullptr, st, false);
+        }
+        TimedScope ts(1, st);
+        const hawkes_status r = narrow_launch(A, c0, c1, nseg, ch == 0, st);
+        if (r != HAWKES_OK) return r;
+    }
+    hipLaunchKernelGGL(large_chunk_acc, dim3(1), dim3(256), 0, st, A.nseg, 4, A.seg_part, A.acc);
+    large_final_launch(A, A.ER, nullptr, A.gpart, A.spart, A.cpart_, A.g_alpha, nullptr, 0, st);
+    return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
+}
+
 hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     if (A.per_target) return run_large_pt(A, st);
     if (A.K > 1) return run_large_multi(A, st);
+    if (A.narrow) return run_narrow(A, st);
     const int32_t M = A.M;
     const int64_t MM = (int64_t)M * M;
     const unsigned gM = (unsigned)((M + 255) / 256);
