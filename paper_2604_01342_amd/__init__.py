@@ -232,6 +232,11 @@ def loglik_grad(t, m, mu, alpha, beta, T, chunk_log2: int = 0, support: bool = F
     """(L, dL/dmu [M], dL/dalpha [M, M], dL/dbeta [1] or [M]) as float64 device tensors.
     support=True: dL/dalpha only at alpha's nonzeros, 0 elsewhere
     (hawkes_loglik_grad_support)."""
+    return _loglik_grad(t, m, mu, alpha, beta, T, chunk_log2, support)
+
+
+def _loglik_grad(t, m, mu, alpha, beta, T, chunk_log2, support=False, packed=False):
+    """loglik_grad; packed: (L, one tensor of the three gradients back to back)."""
     dev, t, m, mu, alpha, beta = _prep(t, m, mu, alpha, beta)
     p = _problem(t, mu, beta, T, chunk_log2, alpha)
     L = lib()
@@ -239,13 +244,18 @@ def loglik_grad(t, m, mu, alpha, beta, T, chunk_log2: int = 0, support: bool = F
     ws = _workspace(dev, nb)
     M = mu.numel()
     out = torch.empty(1, dtype=torch.float64, device=dev)
-    gmu = torch.empty(M, dtype=torch.float64, device=dev)
-    ga = torch.empty(_gshape(mu, alpha), dtype=torch.float64, device=dev)
-    gb = torch.empty(beta.numel(), dtype=torch.float64, device=dev)
+    if packed:
+        na = alpha.numel()
+        g = torch.empty(M + na + beta.numel(), dtype=torch.float64, device=dev)
+        gmu, ga, gb = g[:M], g[M:M + na], g[M + na:]
+    else:
+        gmu = torch.empty(M, dtype=torch.float64, device=dev)
+        ga = torch.empty(_gshape(mu, alpha), dtype=torch.float64, device=dev)
+        gb = torch.empty(beta.numel(), dtype=torch.float64, device=dev)
     name = "hawkes_loglik_grad_support" if support else "hawkes_loglik_grad"
     _check(name, getattr(L, name)(ctypes.byref(p), _ptr(t), _ptr(m), _ptr(mu), _ptr(alpha), _ptr(beta), _ptr(out),
                                   _ptr(gmu), _ptr(ga), _ptr(gb), _ptr(ws), nb, _stream(dev)))
-    return out[0], gmu, ga, gb
+    return (out[0], g) if packed else (out[0], gmu, ga, gb)
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20   # HAWKES_NOALLOC_SCRATCH_BYTES
@@ -545,8 +555,8 @@ class HawkesLogLik(torch.autograd.Function):
     def forward(ctx, mu, alpha, beta, t, m, T, chunk_log2=0):
         need = any(ctx.needs_input_grad[:3])
         if need:
-            L, gmu, ga, gb = loglik_grad(t, m, mu, alpha, beta, T, chunk_log2)
-            ctx.save_for_backward(gmu, ga, gb)
+            L, g = _loglik_grad(t, m, mu, alpha, beta, T, chunk_log2, packed=True)
+            ctx.save_for_backward(g)
         else:
             L = loglik(t, m, mu, alpha, beta, T, chunk_log2)
         ctx.shapes = (mu.shape, alpha.shape, beta.shape)
@@ -555,10 +565,21 @@ class HawkesLogLik(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gL):
-        gmu, ga, gb = ctx.saved_tensors
-        (smu, sa, sb), (dmu, da, db) = ctx.shapes, ctx.dtypes
-        return ((gL * gmu).reshape(smu).to(dmu), (gL * ga).reshape(sa).to(da), (gL * gb).reshape(sb).to(db),
-                None, None, None, None)
+        # the three gradients are scaled (and, of one type, converted) as one
+        # tensor: two launches instead of six
+        g, = ctx.saved_tensors
+        g = gL * g
+        sizes = [s.numel() for s in ctx.shapes]
+        if torch.is_grad_enabled() or len(set(ctx.dtypes)) > 1:
+            return (*(x.reshape(s).to(d) for x, s, d in zip(g.split(sizes), ctx.shapes, ctx.dtypes)),
+                    None, None, None, None)
+        g = g.to(ctx.dtypes[0])
+        out, at = [], 0
+        for s, n in zip(ctx.shapes, sizes):
+            # tensors of their own on the shared memory, not views of one
+            out.append(g.new_empty(0).set_(g.untyped_storage(), at, s))
+            at += n
+        return (*out, None, None, None, None)
 
 
 def hawkes_loglik(t, m, mu, alpha, beta, T, chunk_log2: int = 0) -> torch.Tensor:

@@ -47,6 +47,7 @@ struct LargeArgs {
     int32_t* csr_ptr;
     int2* csr_cv;         // nonzeros of alpha by row: (column, float bits of the value)
     float* colsum;
+    int32_t* rcnt;        // [K][M] nonzeros per row (column, per target) of alpha
     double *rk, *dk;      // K > 1: [K][CH] per event of the chunk, R_k and D_k (alpha row . K and . J)
     double* agg;          // [nseg][2M] segment maps (K_run, J_run)
     double* seg_span;     // [nseg] time from the event before the segment to its last event
@@ -106,6 +107,21 @@ struct LargeArgs {
     float* lambda_out;
 };
 
+// arrays a call clears first (large_setup)
+#define HK_NZERO 6
+struct ZeroList {
+    double* p[HK_NZERO];
+    int64_t n[HK_NZERO];
+    void add(double* q, int64_t cnt) {
+        for (int z = 0; z < HK_NZERO; ++z)
+            if (n[z] == 0) {
+                p[z] = q;
+                n[z] = cnt;
+                return;
+            }
+    }
+};
+
 #define HK_SG 32           // segments per scan group
 #define HK_NBO_MAX 256     // node blocks the forward pass can count for the partition
 
@@ -129,7 +145,10 @@ size_t lds_limit();
 hawkes_status allow_lds(const void* kernel, size_t bytes, bool with_static = false);
 // grants the shared-decay dense kernels their LDS
 hawkes_status dense_allow_lds(const LargeArgs& A);
-void large_build_index(int32_t M, const float* alpha, int trans, int32_t* ptr, int2* cv, hipStream_t st);
+// colsums, index: whether column sums and nonzeros per row are wanted
+void large_setup_launch(const LargeArgs& A, int trans, bool colsums, bool index, const ZeroList& Z, hipStream_t st);
+void large_index_launch(const LargeArgs& A, int trans, int32_t* ptr, int2* cv, int4* node_info, float* csc_b,
+                        hipStream_t st);
 // entries between consecutive kernels' packed rows of alpha: even (each
 // kernel's array starts 16-byte aligned for the forward pass's pair loads)
 // and at least one spare entry past the M^2 a dense alpha fills
@@ -149,9 +168,9 @@ void bucket_starts(const LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, int
 void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipStream_t st, bool first,
                         bool sums_only);
 
-// final sums and outputs of kernel k (see large_final); csum: the columns' compensator sums, or null
-void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,
-                        const double* spart, const double* cpart, double* g_alpha, double* csum, int32_t k,
+// final sums and outputs (see large_final); slots: the call-level sums are the
+// segment slots' (else acc); csum: the columns' compensator sums, or null
+void large_final_launch(const LargeArgs& A, bool slots, const double* ebacc, const double* gpart, double* csum,
                         hipStream_t st);
 
 // the chunk's forward pass and gradient for up to HK_NARROW_MAX_M nodes

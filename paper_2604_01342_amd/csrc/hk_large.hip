@@ -37,102 +37,115 @@
 namespace hk {
 
 // ------------------------------------------------------------------ setup
-__global__ void fill_d(double* p, int64_t n, double v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-// colsum[q] = sum_p alpha[p][q]: a workgroup of 16 waves per 64 columns,
-// wave r sums rows r, r+16, ... (coalesced over q), then a fixed-order sum
-__global__ __launch_bounds__(1024) void large_colsum(int32_t M, const float* __restrict__ alpha,
-                                                     float* __restrict__ colsum) {
-    __shared__ double part[16][64];
-    const int lane = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t q = blockIdx.x * 64 + lane;
-    double c = 0.0;
-    if (q < M) {
-#pragma unroll 8
-        for (int32_t p = r; p < M; p += 16) c += (double)alpha[(int64_t)p * M + q];
-    }
-    part[r][lane] = c;
-    __syncthreads();
-    if (r == 0 && q < M) {
-        double v = 0.0;
-        for (int k = 0; k < 16; ++k) v += part[k][lane];
-        colsum[q] = (float)v;
-    }
-}
-
-// csr_ptr[p+1] = nnz of row p (one wave per row, coalesced).  With trans != 0
-// the rows are the columns of alpha (compressed-column form, strided reads).
+// alpha as the passes read it, and the call's cleared state, in two launches
+// (they were one kernel per array, 8 to 12 launches of about 5 us each):
+//   large_setup   workgroups of 16 waves by role: column sums of alpha (64
+//                 columns; wave r sums rows r, r + 16, .., coalesced over the
+//                 columns, then a fixed-order sum), nonzeros per row (16 rows,
+//                 a wave a row), cleared arrays
+//   large_index   a wave a row: the row's start (the sum of the counts before
+//                 it), its nonzeros in column order, and its node record
+//                 (csr begin, csr end, mu, colsum): one 16-byte load per event
+// With trans the rows are the columns of alpha (compressed-column form).
+// blockIdx.y: the decay kernel.
 __device__ __forceinline__ float alpha_at(const float* __restrict__ alpha, int32_t M, int32_t r, int32_t c,
                                           int trans) {
     return trans ? alpha[(int64_t)c * M + r] : alpha[(int64_t)r * M + c];
 }
 
-__global__ __launch_bounds__(64) void large_rowcount(int32_t M, const float* __restrict__ alpha,
-                                                     int32_t* __restrict__ csr_ptr, int trans) {
-    const int32_t p = blockIdx.x;
-    const int lane = threadIdx.x;
-    int32_t cnt = 0;
-    for (int32_t q = lane; q < M; q += 64) cnt += alpha_at(alpha, M, p, q, trans) != 0.0f;
-    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
-    if (lane == 0) {
-        csr_ptr[p + 1] = cnt;
-        if (p == 0) csr_ptr[0] = 0;
-    }
-}
-
-// inclusive scan of csr_ptr[1..M] in one workgroup
-__global__ __launch_bounds__(1024) void large_csr_scan(int32_t M, int32_t* __restrict__ csr_ptr) {
-    __shared__ int32_t sh[1024];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int32_t base = 0; base < M; base += 1024) {
-        const int32_t i = base + threadIdx.x;
-        const int32_t v = i < M ? csr_ptr[i + 1] : 0;
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const int32_t a = (int)threadIdx.x >= d ? sh[threadIdx.x - d] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += a;
-            __syncthreads();
+__global__ __launch_bounds__(1024) void large_setup(int32_t M, const float* __restrict__ alpha, int trans, int32_t NC,
+                                                    int32_t NR, float* __restrict__ colsum,
+                                                    int32_t* __restrict__ rcnt, ZeroList Z) {
+    __shared__ double part[16][64];
+    const int lane = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t k = blockIdx.y;
+    alpha += (int64_t)k * M * M;
+    int32_t blk = blockIdx.x;
+    if (blk < NC) {
+        const int32_t q = blk * 64 + lane;
+        double c = 0.0;
+        if (q < M) {
+#pragma unroll 8
+            for (int32_t p = r; p < M; p += 16) c += (double)alpha[(int64_t)p * M + q];
         }
-        if (i < M) csr_ptr[i + 1] = carry + sh[threadIdx.x];
+        part[r][lane] = c;
         __syncthreads();
-        if (threadIdx.x == 1023) carry += sh[1023];
-        __syncthreads();
+        if (r == 0 && q < M) {
+            double v = 0.0;
+            for (int i = 0; i < 16; ++i) v += part[i][lane];
+            colsum[(int64_t)k * M + q] = (float)v;
+        }
+        return;
     }
+    blk -= NC;
+    if (blk < NR) {
+        const int32_t p = blk * 16 + r;
+        if (p >= M) return;
+        int32_t cnt = 0;
+#pragma unroll 4
+        for (int32_t q = lane; q < M; q += 64) cnt += alpha_at(alpha, M, p, q, trans) != 0.0f;
+        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off, 64);
+        if (lane == 0) rcnt[(int64_t)k * M + p] = cnt;
+        return;
+    }
+    if (k > 0) return;
+    blk -= NR;
+    const int32_t nz = (int32_t)gridDim.x - NC - NR;
+    for (int z = 0; z < HK_NZERO; ++z)
+        for (int64_t i = blk * 1024ll + threadIdx.x; i < Z.n[z]; i += nz * 1024ll) Z.p[z][i] = 0.0;
 }
 
-// one wave per row: compact the nonzeros of row p in column order
-__global__ __launch_bounds__(64) void large_csr_fill(int32_t M, const float* __restrict__ alpha,
-                                                     const int32_t* __restrict__ csr_ptr,
-                                                     int2* __restrict__ csr_cv,
-                                                     int trans) {
-    const int32_t p = blockIdx.x;
-    const int lane = threadIdx.x;
-    int32_t o = csr_ptr[p];
+__global__ __launch_bounds__(1024) void large_index(int32_t M, const float* __restrict__ alpha, int trans,
+                                                    const int32_t* __restrict__ rcnt, int32_t* __restrict__ ptr,
+                                                    int2* __restrict__ cv, int64_t cvs, const float* __restrict__ mu,
+                                                    const float* __restrict__ colsum, int4* __restrict__ node_info,
+                                                    const float* __restrict__ beta, float* __restrict__ csc_b) {
+    const int lane = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t k = blockIdx.y, p = blockIdx.x * 16 + r;
+    if (p >= M) return;
+    alpha += (int64_t)k * M * M;
+    rcnt += (int64_t)k * M;
+    ptr += (int64_t)k * (M + 1);
+    cv += k * cvs;
+    int32_t o = 0;
+#pragma unroll 4
+    for (int32_t i = lane; i < p; i += 64) o += rcnt[i];
+    for (int off = 32; off > 0; off >>= 1) o += __shfl_xor(o, off, 64);
+    const int32_t e = o + rcnt[p];
+    if (lane == 0) {
+        ptr[p] = o;
+        if (p == M - 1) ptr[M] = e;
+        if (node_info)
+            node_info[(int64_t)k * M + p] =
+                make_int4(o, e, __float_as_int(mu[p]), __float_as_int(colsum[(int64_t)k * M + p]));
+    }
     for (int32_t q0 = 0; q0 < M; q0 += 64) {
         const int32_t q = q0 + lane;
         const float a = q < M ? alpha_at(alpha, M, p, q, trans) : 0.0f;
         const uint64_t nz = __ballot(a != 0.0f);
         if (a != 0.0f) {
-            const int32_t r = __builtin_popcountll(nz & (lane ? (~0ull >> (64 - lane)) : 0ull));
-            csr_cv[o + r] = make_int2(q, __float_as_int(a));
+            const int32_t i = o + __builtin_popcountll(nz & (lane ? (~0ull >> (64 - lane)) : 0ull));
+            cv[i] = make_int2(q, __float_as_int(a));
+            if (csc_b) csc_b[i] = beta[q];
         }
         o += __builtin_popcountll(nz);
     }
 }
 
-// node_info[p] = (csr begin, csr end, mu_p, colsum_p): one 16-byte load per event
-__global__ void large_node_info(int32_t M, const int32_t* __restrict__ csr_ptr, const float* __restrict__ mu,
-                                const float* __restrict__ colsum, int4* __restrict__ node_info) {
-    const int32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= M) return;
-    node_info[p] = make_int4(csr_ptr[p], csr_ptr[p + 1], __float_as_int(mu[p]), __float_as_int(colsum[p]));
+void large_setup_launch(const LargeArgs& A, int trans, bool colsums, bool index, const ZeroList& Z, hipStream_t st) {
+    const int32_t NC = colsums ? (A.M + 63) / 64 : 0, NR = index ? (A.M + 15) / 16 : 0;
+    int64_t total = 0;
+    for (int z = 0; z < HK_NZERO; ++z) total += Z.n[z];
+    const int64_t nz = total < 1024 * 1024 ? (total + 4095) / 4096 : 256;
+    hipLaunchKernelGGL(large_setup, dim3((unsigned)(NC + NR + nz), (unsigned)A.K), dim3(1024), 0, st, A.M, A.alpha,
+                       trans, NC, NR, A.colsum, A.rcnt, Z);
+}
+
+void large_index_launch(const LargeArgs& A, int trans, int32_t* ptr, int2* cv, int4* node_info, float* csc_b,
+                        hipStream_t st) {
+    hipLaunchKernelGGL(large_index, dim3((unsigned)((A.M + 15) / 16), (unsigned)A.K), dim3(1024), 0, st, A.M, A.alpha,
+                       trans, A.rcnt, ptr, cv, cv_stride((int64_t)A.M * A.M), A.mu, A.colsum, node_info, A.beta,
+                       csc_b);
 }
 
 // ------------------------------------------------------------------ agg
@@ -764,7 +777,8 @@ __global__ __launch_bounds__(256) void large_chunk_acc(int32_t nseg, int32_t wid
 // and the segment's float64 partials: log-sum, compensator
 // sum_k colsum_k[m_i] (1 - e^{-beta_k (T - t_i)}), and per kernel E_k (its
 // beta-derivative) and sum_i w_i (R_k(i) - beta_k D_k(i)) (eq. 10 per kernel).
-// One workgroup of 256 per segment, fixed-order block sums.
+// One workgroup of 256 per segment, fixed-order block sums, added to the
+// segment slot's sums over the chunks so far (as in large_forward).
 template <bool GRAD, bool INTENS>
 __global__ __launch_bounds__(256) void large_combine(int64_t c0, int64_t c1, int32_t M, int32_t K, double T,
                                                      const double* __restrict__ t,
@@ -808,25 +822,26 @@ __global__ __launch_bounds__(256) void large_combine(int64_t c0, int64_t c1, int
     const int W = 2 + 2 * K;
     double* o = seg_part + (int64_t)s * W;
     double v = block_sum_d<256>(logsum, sh);
-    if (threadIdx.x == 0) o[0] = v;
+    if (threadIdx.x == 0) o[0] += v;
     v = block_sum_d<256>(comp, sh);
-    if (threadIdx.x == 0) o[1] = v;
+    if (threadIdx.x == 0) o[1] += v;
 #pragma unroll
     for (int k = 0; k < HK_KMAX; ++k) {
         if (k < K) {
             v = block_sum_d<256>(E[k], sh);
-            if (threadIdx.x == 0) o[2 + k] = v;
+            if (threadIdx.x == 0) o[2 + k] += v;
             v = block_sum_d<256>(gb[k], sh);
-            if (threadIdx.x == 0) o[2 + K + k] = v;
+            if (threadIdx.x == 0) o[2 + K + k] += v;
         }
     }
 }
 
 // ------------------------------------------------------------------ finalize
-// Final sums of kernel k of K (decay kernels): the log-likelihood and dL/dmu
-// with k = 0, dL/dbeta, dL/dalpha from the partials (g_alpha, gpart and cpart
-// point at kernel k's).  acc: the call-level sums (logsum, comp, E[K],
-// gbeta[K]); ebacc: per-target decays, dL/dbeta = -ebacc, else null.
+// Final sums, blockIdx.z = kernel k of K (decay kernels): the log-likelihood and
+// dL/dmu with k = 0, dL/dbeta, dL/dalpha from the partials.  The call-level
+// sums (logsum, comp, E[K], gbeta[K]) are those of the nslot segment slots
+// seg_part[nslot][2 + 2K], summed here by a fixed tree, or (seg_part null) acc;
+// ebacc: per-target decays, dL/dbeta = -ebacc, else null.
 // Every entry is summed over ER partials of dL/dalpha, and its column over NSC
 // partials of the weights and compensator terms, each in a fixed order: a
 // workgroup takes 16 columns and FR rows, its 16 thread rows are ES
@@ -849,30 +864,65 @@ __device__ __forceinline__ double fin_tree(double v, double (*sh)[17], int c, in
 }
 
 __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_t NSC, int32_t ES, double T,
-                                                   const float* __restrict__ mu, const double* __restrict__ acc,
+                                                   const float* __restrict__ mu, const double* __restrict__ seg_part,
+                                                   int32_t nslot, const double* __restrict__ acc,
                                                    const double* __restrict__ ebacc, const double* __restrict__ gpart,
                                                    const double* __restrict__ spart,
                                                    const double* __restrict__ cpart, double* __restrict__ loglik,
                                                    double* __restrict__ g_mu, double* __restrict__ g_alpha,
                                                    double* __restrict__ g_beta, double* __restrict__ csum, int grad,
-                                                   int32_t K, int32_t k, int32_t FR) {
+                                                   int32_t K, int32_t NSP, int32_t FR) {
     __shared__ double sh[16][17];
     __shared__ double ps[256];
     const int64_t MM = (int64_t)M * M;
     const int c = threadIdx.x & 15, s = threadIdx.x >> 4;
+    const int32_t k = blockIdx.z;
+    if (gpart) gpart += (int64_t)k * ER * MM;
+    if (grad) {
+        spart += (int64_t)k * NSP * M;
+        cpart += (int64_t)k * NSP * M;
+        if (g_alpha) g_alpha += (int64_t)k * MM;
+    }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        // sum of mu in a fixed order: strided partial sums, then a tree
+        // sums in a fixed order: strided partial sums, then a tree
+        auto total = [&](double v) {
+            ps[threadIdx.x] = v;
+            __syncthreads();
+            for (int h = 128; h > 0; h >>= 1) {
+                if ((int)threadIdx.x < h) ps[threadIdx.x] += ps[threadIdx.x + h];
+                __syncthreads();
+            }
+            const double r = ps[0];
+            __syncthreads();
+            return r;
+        };
         double v = 0.0;
         for (int32_t p = threadIdx.x; p < M; p += 256) v += (double)mu[p];
-        ps[threadIdx.x] = v;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) ps[threadIdx.x] += ps[threadIdx.x + h];
-            __syncthreads();
+        const double musum = total(v);
+        const int32_t W = 2 + 2 * K;
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+        if (seg_part) {
+#pragma unroll 4
+            for (int32_t i = threadIdx.x; i < nslot; i += 256) {
+                const double* o = seg_part + (int64_t)i * W;
+                a0 += o[0];
+                a1 += o[1];
+                a2 += o[2 + k];
+                a3 += o[2 + K + k];
+            }
+            a0 = total(a0);
+            a1 = total(a1);
+            a2 = total(a2);
+            a3 = total(a3);
+        } else {
+            a0 = acc[0];
+            a1 = acc[1];
+            a2 = acc[2 + k];
+            a3 = acc[2 + K + k];
         }
         if (threadIdx.x == 0) {
-            if (k == 0) loglik[0] = acc[0] - T * ps[0] - acc[1];
-            if (grad && g_beta && !ebacc) g_beta[k] = acc[2 + K + k] - acc[2 + k];
+            if (k == 0) loglik[0] = a0 - T * musum - a1;
+            if (grad && g_beta && !ebacc) g_beta[k] = a3 - a2;
         }
     }
     if (!grad) return;
@@ -917,8 +967,7 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
     }
 }
 
-void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, const double* gpart,
-                        const double* spart, const double* cpart, double* g_alpha, double* csum, int32_t k,
+void large_final_launch(const LargeArgs& A, bool slots, const double* ebacc, const double* gpart, double* csum,
                         hipStream_t st) {
     // slices of the partials: enough that a slice sums at most about 8, as
     // long as that leaves a slice several
@@ -926,12 +975,15 @@ void large_final_launch(const LargeArgs& A, int32_t NSC, const double* ebacc, co
     while (ES < 16 && A.ER > 8 * ES) ES <<= 1;
     // rows per workgroup: 16, or one pass of its thread rows where that leaves
     // the chip idle (few nodes)
-    const unsigned gx = (unsigned)((A.M + 15) / 16);
+    const int32_t M = A.M;
+    const unsigned gx = (unsigned)((M + 15) / 16);
     const int32_t FR = (int64_t)gx * gx < 256 ? 16 / ES : 16;
-    const unsigned gy = (unsigned)((A.M + FR - 1) / FR);
-    hipLaunchKernelGGL(large_final, A.grad ? dim3(gx, g_alpha ? gy : 1) : dim3(1), dim3(256), 0, st, A.M, A.ER, NSC,
-                       ES, A.T, A.mu, A.acc, ebacc, gpart, spart, cpart, A.loglik, A.g_mu, g_alpha, A.g_beta, csum,
-                       A.grad ? 1 : 0, A.K, k, FR);
+    const unsigned gy = (unsigned)((M + FR - 1) / FR);
+    const unsigned gz = (unsigned)A.K;
+    hipLaunchKernelGGL(large_final, A.grad ? dim3(gx, A.g_alpha ? gy : 1, gz) : dim3(1), dim3(256), 0, st, M, A.ER,
+                       A.ER, ES, A.T, A.mu, slots ? A.seg_part : (const double*)nullptr, A.nseg, A.acc, ebacc, gpart,
+                       A.spart, A.cpart_, A.loglik, A.g_mu, A.g_alpha, A.g_beta, csum, A.grad ? 1 : 0, A.K, A.NSP,
+                       FR);
 }
 
 // support-restricted dL/dalpha: one wave per row p writes, for each nonzero
@@ -1037,6 +1089,7 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     A.csr_ptr = c.take<int32_t>(K * (M + 1));
     A.csr_cv = c.take<int2>(K * cv_stride(MM));
     A.colsum = c.take<float>(K * M);
+    A.rcnt = c.take<int32_t>(K * M);
     if (K > 1) {
         A.rk = c.take<double>((size_t)K * A.CH);
         if (grad) A.dk = c.take<double>((size_t)K * A.CH);
@@ -1164,12 +1217,6 @@ hawkes_status allow_lds(const void* kernel, size_t bytes, bool with_static) {
     return HAWKES_OK;
 }
 
-void large_build_index(int32_t M, const float* alpha, int trans, int32_t* ptr, int2* cv, hipStream_t st) {
-    hipLaunchKernelGGL(large_rowcount, dim3(M), dim3(64), 0, st, M, alpha, ptr, trans);
-    hipLaunchKernelGGL(large_csr_scan, dim3(1), dim3(1024), 0, st, M, ptr);
-    hipLaunchKernelGGL(large_csr_fill, dim3(M), dim3(64), 0, st, M, alpha, ptr, cv, trans);
-}
-
 void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st, bool apply) {
     const int32_t M = A.M;
     // the first two passes are serial chains per thread, ngr * M and M
@@ -1193,17 +1240,12 @@ void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st
 // lambda and the shared w_i = 1/lambda_i; with the gradient the chunk's events
 // are partitioned once and the dense dL/dalpha kernels run once per kernel
 // (decay beta_k, kernel k's state checkpoints and partial sums).
-static void fill_launch(double* p, int64_t n, hipStream_t st) {
-    const int64_t nb = (n + 255) / 256;
-    hipLaunchKernelGGL(fill_d, dim3((unsigned)(nb < 65535 ? nb : 65535)), dim3(256), 0, st, p, n, 0.0);
-}
-
 // the dense gradient's partials of a sequence without events (otherwise the
 // first chunk stores them)
-static void dense_zero(const LargeArgs& A, hipStream_t st) {
-    fill_launch(A.gpart, (int64_t)A.K * A.ER * A.M * A.M, st);
-    fill_launch(A.spart, (int64_t)A.K * A.NSP * A.M, st);
-    fill_launch(A.cpart_, (int64_t)A.K * A.NSP * A.M, st);
+static void dense_zero(const LargeArgs& A, ZeroList& Z) {
+    Z.add(A.gpart, (int64_t)A.K * A.ER * A.M * A.M);
+    Z.add(A.spart, (int64_t)A.K * A.NSP * A.M);
+    Z.add(A.cpart_, (int64_t)A.K * A.NSP * A.M);
 }
 
 static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
@@ -1218,19 +1260,14 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
         return HAWKES_EUNSUPPORTED;
     if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const int32_t W = 2 + 2 * K;
-    hipLaunchKernelGGL(fill_d, dim3(16), dim3(256), 0, st, A.carry, (int64_t)K * 2 * M, 0.0);
-    hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)W, 0.0);
-    if (A.grad && A.nchunks == 0) dense_zero(A, st);
-    // per kernel: column sums, CSR copy and node records of alpha^k
-    for (int32_t k = 0; k < K; ++k) {
-        const float* ak = A.alpha + (int64_t)k * MM;
-        int32_t* pk = A.csr_ptr + (int64_t)k * (M + 1);
-        hipLaunchKernelGGL(large_colsum, dim3((unsigned)((M + 63) / 64)), dim3(1024), 0, st, M, ak,
-                           A.colsum + (int64_t)k * M);
-        large_build_index(M, ak, 0, pk, A.csr_cv + k * cv_stride(MM), st);
-        hipLaunchKernelGGL(large_node_info, dim3(gM), dim3(256), 0, st, M, pk, A.mu, A.colsum + (int64_t)k * M,
-                           A.node_info + (int64_t)k * M);
-    }
+    // cleared: the carried states and the segment slots' sums over the chunks
+    ZeroList Z{};
+    Z.add(A.carry, (int64_t)K * 2 * M);
+    Z.add(A.seg_part, (int64_t)A.nseg * W);
+    if (A.grad && A.nchunks == 0) dense_zero(A, Z);
+    // column sums, CSR copies and node records of every alpha^k
+    large_setup_launch(A, 0, true, true, Z, st);
+    large_index_launch(A, 0, A.csr_ptr, A.csr_cv, A.node_info, nullptr, st);
     // kernel k's view of the per-kernel arrays
     auto view = [&](int32_t k) {
         LargeArgs B = A;
@@ -1291,7 +1328,6 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
                                    A.t, A.marks, A.mu, A.beta, A.colsum, A.rk, A.dk, A.CH, A.seg_part, A.wchunk,
                                    (float*)nullptr);
         }
-        hipLaunchKernelGGL(large_chunk_acc, dim3(1), dim3(256), 0, st, nseg, W, A.seg_part, A.acc);
         if (A.grad) {
             {
                 TimedScope tb(6, st);
@@ -1303,13 +1339,7 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
             }
         }
     }
-    for (int32_t k = 0; k < K; ++k) {
-        LargeArgs B = view(k);
-        B.K = K;
-        large_final_launch(B, A.ER, nullptr, B.gpart, B.spart, B.cpart_, A.g_alpha ? A.g_alpha + k * MM : nullptr,
-                           nullptr, k, st);
-        if (!A.grad) break;   // the log-likelihood needs one launch
-    }
+    large_final_launch(A, true, nullptr, A.gpart, nullptr, st);
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
@@ -1317,11 +1347,11 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
 // one kernel per chunk
 static hawkes_status run_narrow(LargeArgs& A, hipStream_t st) {
     const int32_t M = A.M;
-    hipLaunchKernelGGL(fill_d, dim3(1), dim3(256), 0, st, A.carry, (int64_t)2 * M, 0.0);
-    hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)4, 0.0);
-    hipLaunchKernelGGL(fill_d, dim3(4), dim3(256), 0, st, A.seg_part, (int64_t)A.nseg * 4, 0.0);
-    if (A.grad && A.nchunks == 0) dense_zero(A, st);
-    hipLaunchKernelGGL(large_colsum, dim3((unsigned)((M + 63) / 64)), dim3(1024), 0, st, M, A.alpha, A.colsum);
+    ZeroList Z{};
+    Z.add(A.carry, (int64_t)2 * M);
+    Z.add(A.seg_part, (int64_t)A.nseg * 4);
+    if (A.grad && A.nchunks == 0) dense_zero(A, Z);
+    large_setup_launch(A, 0, true, false, Z, st);
     for (int64_t ch = 0; ch < A.nchunks; ++ch) {
         const int64_t c0 = ch * A.CH;
         const int64_t c1 = c0 + A.CH < A.n ? c0 + A.CH : A.n;
@@ -1339,8 +1369,7 @@ static hawkes_status run_narrow(LargeArgs& A, hipStream_t st) {
         const hawkes_status r = narrow_launch(A, c0, c1, nseg, ch == 0, st);
         if (r != HAWKES_OK) return r;
     }
-    hipLaunchKernelGGL(large_chunk_acc, dim3(1), dim3(256), 0, st, A.nseg, 4, A.seg_part, A.acc);
-    large_final_launch(A, A.ER, nullptr, A.gpart, A.spart, A.cpart_, A.g_alpha, nullptr, 0, st);
+    large_final_launch(A, true, nullptr, A.gpart, nullptr, st);
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
@@ -1365,12 +1394,6 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     // of the dense partials, up to 8 of them (a power of two)
     const int32_t ncopy = A.ER >= 8 ? 8 : A.ER >= 4 ? 4 : A.ER >= 2 ? 2 : 1;
     if (sup) A.gsup = A.gpart;
-    // zero the carried state and accumulators
-    hipLaunchKernelGGL(fill_d, dim3(1), dim3(256), 0, st, A.carry, (int64_t)2 * M, 0.0);
-    hipLaunchKernelGGL(fill_d, dim3(1), dim3(64), 0, st, A.acc, (int64_t)4, 0.0);
-    // per-segment-slot sums of the forward pass, accumulated over the chunks
-    // (one reduction after the last chunk instead of one launch per chunk)
-    hipLaunchKernelGGL(fill_d, dim3(4), dim3(256), 0, st, A.seg_part, (int64_t)A.nseg * 4, 0.0);
     // the forward pass adds the scan's group carries itself (the scan's
     // apply pass is left out) and counts the partition (by blocks of 2^DRB
     // nodes, when the gradient needs them and they fit its LDS).  Measured
@@ -1394,11 +1417,15 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
         }
     }
     A.carry_prefix = true;
-    if (A.grad && A.nchunks == 0) dense_zero(A, st);
-    if (sup) fill_launch(A.gsup, ncopy * MM, st);   // the CSR-ordered sums
-    hipLaunchKernelGGL(large_colsum, dim3((unsigned)((M + 63) / 64)), dim3(1024), 0, st, M, A.alpha, A.colsum);
-    large_build_index(M, A.alpha, 0, A.csr_ptr, A.csr_cv, st);
-    hipLaunchKernelGGL(large_node_info, dim3(gM), dim3(256), 0, st, M, A.csr_ptr, A.mu, A.colsum, A.node_info);
+    // cleared: the carried state, the segment slots' sums over the chunks (one
+    // reduction after the last chunk) and the CSR-ordered sums
+    ZeroList Z{};
+    Z.add(A.carry, (int64_t)2 * M);
+    Z.add(A.seg_part, (int64_t)A.nseg * 4);
+    if (A.grad && A.nchunks == 0) dense_zero(A, Z);
+    if (sup) Z.add(A.gsup, ncopy * MM);
+    large_setup_launch(A, 0, true, true, Z, st);
+    large_index_launch(A, 0, A.csr_ptr, A.csr_cv, A.node_info, nullptr, st);
     for (int64_t ch = 0; ch < A.nchunks; ++ch) {
         const int64_t c0 = ch * A.CH;
         const int64_t c1 = c0 + A.CH < A.n ? c0 + A.CH : A.n;
@@ -1448,8 +1475,7 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
             large_dense_launch(A, c0, c1, nseg, st, ch == 0, sup);
         }
     }
-    hipLaunchKernelGGL(large_chunk_acc, dim3(1), dim3(256), 0, st, A.nseg, 4, A.seg_part, A.acc);
-    large_final_launch(A, A.ER, nullptr, sup ? nullptr : A.gpart, A.spart, A.cpart_, A.g_alpha, A.csum, 0, st);
+    large_final_launch(A, true, nullptr, sup ? nullptr : A.gpart, A.csum, st);
     if (sup && A.g_alpha)
         hipLaunchKernelGGL(large_sup_scatter, dim3((unsigned)M), dim3(64), 0, st, M, ncopy, A.csr_ptr, A.csr_cv,
                            A.gsup, A.csum, A.g_alpha);

@@ -76,24 +76,10 @@ __device__ __forceinline__ int32_t wave_incl_scan_dpp(int32_t v) {
     return v;
 }
 
-__global__ void pt_fill(double* p, int64_t n, double v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 // dst[i] = src[i] (a chunk-start state into or out of a checkpoint slot)
 __global__ void pt_copy(double* __restrict__ dst, const double* __restrict__ src, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = src[i];
-}
-
-// csc_b[k] = beta of the target of column entry k (the decay that entry's
-// push uses, so a pass reads it with the entry instead of a second gather)
-__global__ void pt_csc_beta(int32_t M, const int32_t* __restrict__ csc_ptr, const int2* __restrict__ csc_cv,
-                            const float* __restrict__ beta, float* __restrict__ csc_b) {
-    const int32_t nnz = csc_ptr[M];
-    for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += gridDim.x * blockDim.x)
-        csc_b[k] = beta[csc_cv[k].x];
 }
 
 // adjoint seed at T: A_p(T) = 1 / beta_p
@@ -1250,24 +1236,20 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
         return HAWKES_EUNSUPPORTED;
     // the gradient's two checkpoint levels hold at most HK_PTCK^2 chunks
     if (A.grad && A.pt_ckr > HK_PTCK) return HAWKES_EUNSUPPORTED;
-    auto fill = [&](double* p, int64_t cnt, double v) {
-        const int64_t nb = (cnt + 255) / 256;
-        hipLaunchKernelGGL(pt_fill, dim3((unsigned)(nb < 65535 ? (nb > 0 ? nb : 1) : 65535)), dim3(256), 0, st, p,
-                           cnt, v);
-    };
-    fill(A.carry, 2 * (int64_t)M, 0.0);
-    fill(A.acc, 4, 0.0);
-    fill(A.ebacc, M, 0.0);
+    ZeroList Z{};
+    Z.add(A.carry, 2 * (int64_t)M);
+    Z.add(A.acc, 4);
+    Z.add(A.ebacc, M);
     if (A.grad) {
-        fill(A.gpart, (int64_t)A.ER * MM, 0.0);
-        fill(A.spart, (int64_t)A.ER * M, 0.0);
-        fill(A.cpart_, (int64_t)A.ER * M, 0.0);
+        Z.add(A.gpart, (int64_t)A.ER * MM);
+        Z.add(A.spart, (int64_t)A.ER * M);
+        Z.add(A.cpart_, (int64_t)A.ER * M);
     }
-    large_build_index(M, A.alpha, 1, A.csc_ptr, A.csc_cv, st);
+    large_setup_launch(A, 1, false, true, Z, st);
     // the per-target engine builds no row index: its buffer holds the decay
     // of every column entry's target
     float* csc_b = reinterpret_cast<float*>(A.csr_cv);
-    hipLaunchKernelGGL(pt_csc_beta, dim3(1024), dim3(256), 0, st, M, A.csc_ptr, A.csc_cv, A.beta, csc_b);
+    large_index_launch(A, 1, A.csc_ptr, A.csc_cv, nullptr, csc_b, st);
     // beta_min and a chunk's flag (near T or not)
     float* flags = A.pt_flags;
     hipLaunchKernelGGL(pt_bmin, dim3(1), dim3(256), 0, st, M, A.beta, flags);
@@ -1406,7 +1388,7 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
             }
         }
     }
-    large_final_launch(A, A.ER, A.ebacc, A.gpart, A.spart, A.cpart_, A.g_alpha, nullptr, 0, st);
+    large_final_launch(A, false, A.ebacc, A.gpart, nullptr, st);
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
