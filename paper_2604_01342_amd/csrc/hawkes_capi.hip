@@ -27,33 +27,28 @@ static int32_t pow2_at_least(int32_t m) {
     return p;
 }
 
-// single-sequence descriptor written on the device so calls stay graph-capturable
-__global__ void write_single_desc(int64_t n, int32_t m, double T, int64_t* ev_off, int32_t* m_s,
-                                  double* T_s) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        ev_off[0] = 0;
-        ev_off[1] = n;
-        m_s[0] = m;
-        T_s[0] = T;
-    }
-}
-
 size_t small_layout(SmallArgs& A, int32_t S, int64_t n_total, int32_t max_m, bool grad, void* ws,
                     size_t ws_bytes, bool single) {
     A.S = S;
     A.MP = pow2_at_least(max_m < 1 ? 1 : max_m);
     // events per item: at least 16; for long inputs grow it so the item count
-    // (and so the workspace) stays bounded: the workspace does not grow with n
-    // beyond 64Ki items per sequence block.
+    // (and so the workspace) stays bounded.  A longer item is a longer serial
+    // walk, more items are a longer chain over the waves' maps (one sequence)
+    // and more partials to add.  Us a call with 16 / 32 / 64 / 128 events, one
+    // sequence: 1e6 events, M = 1: 184 / 119 / 102 / 125, M = 5: 232 / 151 /
+    // 119 / 138; 1e5, M = 8: 63 / 63 / 89 / 126; batches: 2.9e6 events in 200:
+    // 114 / 92 / 94 / 109; 6.3e7 in 4096 with 256 / 512 / 1024: 1240 / 1198 /
+    // 1184.
     int64_t L = 16;
-    const int64_t target_items = single ? 65536 : 262144;
+    const int64_t target_items = single ? 24576 : 131072;
     while (L < 4096 && n_total / L > target_items) L <<= 1;
     if (n_total / L > target_items) L = (n_total + target_items - 1) / target_items;
-    // a tuned item length replaces this one unless it breaks the item bound
+    // a tuned item length replaces this one unless it makes more items than the
+    // workspace is meant for
     const hawkes_tuning tu = tuning_snapshot();
     if (tu.item_log2 > 0) {
         const int64_t Lt = (int64_t)1 << tu.item_log2;
-        if (Lt >= L || n_total / Lt <= target_items) L = Lt;
+        if (Lt >= L || n_total / Lt <= (single ? 65536 : 262144)) L = Lt;
     }
     A.L = (int32_t)L;
     A.n_total = n_total;
@@ -210,8 +205,9 @@ static hawkes_status run_single(const hawkes_problem* p, const double* t, const 
         const size_t need = small_layout(A, 1, p->n, p->m, grad, ws, ws_bytes, true);
         if (ws_bytes < need) return HAWKES_EWORKSPACE;
         if (((uintptr_t)ws & 255) != 0) return HAWKES_EWORKSPACE;
-        hipLaunchKernelGGL(write_single_desc, dim3(1), dim3(64), 0, stream, p->n, p->m, p->T,
-                           (int64_t*)A.ev_off, (int32_t*)A.m_s, (double*)A.T_s);
+        A.single = true;
+        A.m1 = p->m;
+        A.T1 = p->T;
         A.t = t; A.marks = marks; A.mu = mu; A.alpha = alpha; A.beta = beta;
         A.loglik = loglik ? loglik : A.ll_scratch;
         A.g_mu = g_mu; A.g_alpha = g_alpha; A.g_beta = g_beta;

@@ -31,6 +31,9 @@ struct SmallArgs {
     int32_t MP;          // padded node count: 1, 2, 4 or 8
     int32_t L;           // events per item
     int64_t n_total;
+    bool single;         // one sequence, its node count m1 and window end T1 given here
+    int32_t m1;
+    double T1;
     int64_t n_items_cap, n_chunks_cap;
     bool grad;
     const int64_t* ev_off;

@@ -41,51 +41,98 @@ __device__ __forceinline__ void seq_range(const int64_t* __restrict__ ev_off, in
     *e1 = b;
 }
 
+// Inclusive sum over the 64 lanes of a wave on the vector ALU (DPP row shifts,
+// then the rows' totals carried forward; a lane that a step does not reach
+// adds 0); every lane active.
+__device__ __forceinline__ int32_t scan64(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
+// One sequence given by value (d_off set): its descriptor arrays are written
+// here too (device arrays, so that calls stay graph-capturable).
 __global__ __launch_bounds__(1024) void small_setup(int32_t S, int64_t n_total, const int64_t* __restrict__ ev_off,
                                                     const int32_t* __restrict__ m_s, int32_t L,
                                                     int64_t* __restrict__ item_off,
                                                     int64_t* __restrict__ chunk_off,
                                                     int64_t* __restrict__ mu_off,
-                                                    int64_t* __restrict__ a_off) {
-    __shared__ int64_t sh[4][1024];
-    __shared__ int64_t carry[4];
-    if (threadIdx.x < 4) carry[threadIdx.x] = 0;
-    __syncthreads();
+                                                    int64_t* __restrict__ a_off, int64_t* __restrict__ d_off,
+                                                    int32_t* __restrict__ d_m, double* __restrict__ d_T, int32_t m1,
+                                                    double T1) {
+    if (d_off) {
+        if (threadIdx.x == 0) {
+            const int64_t items = n_total > 0 ? (n_total + L - 1) / L : 0;
+            const int64_t mm = m1 < 1 ? 1 : m1;
+            d_off[0] = 0;
+            d_off[1] = n_total;
+            d_m[0] = m1;
+            d_T[0] = T1;
+            item_off[0] = chunk_off[0] = mu_off[0] = a_off[0] = 0;
+            item_off[1] = items;
+            chunk_off[1] = (items + HK_RCH - 1) / HK_RCH;
+            mu_off[1] = mm;
+            a_off[1] = mm * mm;
+        }
+        return;
+    }
+    // sums of items, chunks, nodes, and nodes squared as two parts of 24 bits
+    // and up (so that every scan runs in 32 bits: a wave's sum of 64 stays
+    // below 2^31).  Bound by the chain of steps: 1024 sequences are two
+    // barriers and some 20 DPP steps (48 sequences 3.1 us, 4096 14 us; as ten
+    // rounds of LDS and barriers 6.3 and 26 us)
+    __shared__ int32_t wt[5][16];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int64_t carry[4] = {0, 0, 0, 0};
     for (int32_t base = 0; base < S; base += 1024) {
         const int32_t s = base + (int32_t)threadIdx.x;
-        int64_t v[4] = {0, 0, 0, 0};
+        int32_t v[5] = {0, 0, 0, 0, 0}, x[5];
         if (s < S) {
             int64_t e0, e1;
             seq_range(ev_off, s, n_total, &e0, &e1);
             const int64_t len = e1 - e0;
-            const int64_t items = len > 0 ? (len + L - 1) / L : 0;
+            const int32_t items = len <= 0 ? 0
+                                  : len < (1 << 30) ? ((int32_t)len + L - 1) / L
+                                                    : (int32_t)((len + L - 1) / L);
             const int64_t mm = m_s[s] < 1 ? 1 : m_s[s];
             v[0] = items;
             v[1] = (items + HK_RCH - 1) / HK_RCH;
-            v[2] = mm;
-            v[3] = mm * mm;
+            v[2] = (int32_t)mm;
+            v[3] = (int32_t)(mm * mm & 0xffffff);
+            v[4] = (int32_t)(mm * mm >> 24);
         }
-        for (int k = 0; k < 4; ++k) sh[k][threadIdx.x] = v[k];
+        // inclusive scan over the wave's lanes, then over the waves' totals
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            x[k] = scan64(v[k]);
+            if (lane == 63) wt[k][wid] = x[k];
+        }
         __syncthreads();
-        // inclusive Hillis-Steele scan in shared memory
-        for (int d = 1; d < 1024; d <<= 1) {
-            int64_t add[4] = {0, 0, 0, 0};
-            if ((int)threadIdx.x >= d)
-                for (int k = 0; k < 4; ++k) add[k] = sh[k][threadIdx.x - d];
-            __syncthreads();
-            for (int k = 0; k < 4; ++k) sh[k][threadIdx.x] += add[k];
-            __syncthreads();
+        int64_t before[5], tot[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            // lanes 0..15 hold the waves' totals (64-bit sums in two parts)
+            const int32_t y = wt[k][lane & 15];
+            const int32_t lo = scan64(lane < 16 ? y & 0xffff : 0), hi = scan64(lane < 16 ? y >> 16 : 0);
+            const int64_t incl = (int64_t)lo + ((int64_t)hi << 16);
+            before[k] = (int64_t)__shfl((long long)incl, wid, 64) - wt[k][wid];
+            tot[k] = (int64_t)__shfl((long long)incl, 15, 64);
         }
         if (s < S) {
-            item_off[s] = carry[0] + sh[0][threadIdx.x] - v[0];
-            chunk_off[s] = carry[1] + sh[1][threadIdx.x] - v[1];
-            mu_off[s] = carry[2] + sh[2][threadIdx.x] - v[2];
-            a_off[s] = carry[3] + sh[3][threadIdx.x] - v[3];
+            item_off[s] = carry[0] + before[0] + x[0] - v[0];
+            chunk_off[s] = carry[1] + before[1] + x[1] - v[1];
+            mu_off[s] = carry[2] + before[2] + x[2] - v[2];
+            a_off[s] = carry[3] + before[3] + x[3] - v[3] + ((before[4] + x[4] - v[4]) << 24);
         }
-        __syncthreads();
-        if (threadIdx.x == 1023)
-            for (int k = 0; k < 4; ++k) carry[k] += sh[k][1023];
-        __syncthreads();
+        carry[0] += tot[0];
+        carry[1] += tot[1];
+        carry[2] += tot[2];
+        carry[3] += tot[3] + (tot[4] << 24);
+        __syncthreads();   // wt is reused
     }
     if (threadIdx.x == 0) {
         item_off[S] = carry[0];
@@ -343,16 +390,32 @@ __global__ __launch_bounds__(256) void small_tile_scan(int32_t S, int64_t n_item
     const double bet = (double)beta[s];
     const int W = 2 + 2 * MP;
     double K = tile_agg[t0 * W + 2 + q], J = tile_agg[t0 * W + 2 + MP + q];
-    for (int64_t tt = t0 + 1; tt <= t1; ++tt) {
-        tile_carry[tt * 2 * MP + q] = K;
-        tile_carry[tt * 2 * MP + MP + q] = J;
-        if (tt == t1) break;
-        const double D = tile_agg[tt * W + 0];
-        const double ex = exp(-bet * D);
-        const double Kb = tile_agg[tt * W + 2 + q], Jb = tile_agg[tt * W + 2 + MP + q];
-        const double k0 = K;
-        K = __builtin_fma(ex, k0, Kb);
-        J = __builtin_fma(ex, __builtin_fma(D, k0, J), Jb);
+    // 16 tiles at a time, their loads and decays before the chain: two
+    // multiply-adds a tile remain in series (one load and exponential a tile
+    // in series: 130 us for the 977 tiles of 1e6 events)
+    constexpr int PF = 16;
+    for (int64_t tb = t0 + 1; tb <= t1; tb += PF) {
+        double D[PF], ex[PF], Kb[PF], Jb[PF];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int64_t tt = tb + u < t1 ? tb + u : t1;
+            D[u] = tile_agg[tt * W + 0];
+            Kb[u] = tile_agg[tt * W + 2 + q];
+            Jb[u] = tile_agg[tt * W + 2 + MP + q];
+        }
+#pragma unroll
+        for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bet * D[u]);
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int64_t tt = tb + u;
+            if (tt <= t1) {
+                tile_carry[tt * 2 * MP + q] = K;
+                tile_carry[tt * 2 * MP + MP + q] = J;
+                const double k0 = K;
+                K = __builtin_fma(ex[u], k0, Kb[u]);
+                J = __builtin_fma(ex[u], __builtin_fma(D[u], k0, J), Jb[u]);
+            }
+        }
     }
 }
 
@@ -778,7 +841,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 // a partial (1024 / PW slices), slice sums are added in slice order.  Bound by
 // the read of the partials; with one thread per entry the chunk's 256 items
 // were 256 dependent rounds of loads (48 sequences of 100 to 2000 events:
-// 29 us, 6 us now; 4096 sequences, 246,000 items: 121 us, 45 us now).
+// 29 us, 6 us now; 4096 sequences, 123,000 items: 41 us for 139 MB of partials).
 __global__ __launch_bounds__(1024) void small_reduce1(int32_t S, int64_t n_items_cap,
                                                      const int64_t* __restrict__ item_off,
                                                      const int64_t* __restrict__ chunk_off,
@@ -809,9 +872,11 @@ __global__ __launch_bounds__(1024) void small_reduce1(int32_t S, int64_t n_items
     }
 }
 
-// level 2: per sequence; assemble eqs. 2, 8, 9, 10
+// level 2: per sequence, the chunks' sums (few items in all: the items'
+// themselves) by slices as in level 1 (blockDim / PW of them; one slice for
+// 244 chunks took about 80 us); assemble eqs. 2, 8, 9, 10
 template <int MP, bool GRAD>
-__global__ __launch_bounds__(128) void small_reduce2(int32_t S, int64_t n_chunks_cap,
+__global__ __launch_bounds__(1024) void small_reduce2(int32_t S, int64_t n_chunks_cap,
                                                     const int64_t* __restrict__ chunk_off,
                                                     const int32_t* __restrict__ m_s, const double* __restrict__ T_s,
                                                     const float* __restrict__ mu, const float* __restrict__ beta,
@@ -822,13 +887,22 @@ __global__ __launch_bounds__(128) void small_reduce2(int32_t S, int64_t n_chunks
     const int32_t s = blockIdx.x;
     if (s >= S) return;
     __shared__ double tot[4 + 2 * MP + MP * MP];
+    __shared__ double sh[1024];
     const int64_t c0 = chunk_off[s];
     int64_t c1 = chunk_off[s + 1];
     c1 = c1 > n_chunks_cap ? n_chunks_cap : c1;
-    for (int e = threadIdx.x; e < PW; e += blockDim.x) {
-        double acc = 0.0;
-        for (int64_t c = c0; c < c1; ++c) acc += cpart[c * PW + e];
-        tot[e] = acc;
+    const int ns = (int)blockDim.x / PW, e = threadIdx.x % PW, sl = threadIdx.x / PW;
+    double acc = 0.0;
+    if (sl < ns) {
+#pragma unroll 4
+        for (int64_t c = c0 + sl; c < c1; c += ns) acc += cpart[c * PW + e];
+    }
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    if ((int)threadIdx.x < PW) {
+        double v = 0.0;
+        for (int k = 0; k < ns; ++k) v += sh[k * PW + threadIdx.x];
+        tot[threadIdx.x] = v;
     }
     __syncthreads();
     const int32_t M = m_s[s] < 1 ? 1 : (m_s[s] > MP ? MP : m_s[s]);
@@ -858,8 +932,9 @@ static hawkes_status run_small_mp(const SmallArgs& A, hipStream_t st) {
     const int64_t waves = (A.n_items_cap + 63) / 64;
     const int64_t blocks = (waves + 3) / 4;
     TimedScope* t5 = new TimedScope(5, st);
-    hipLaunchKernelGGL(small_setup, dim3(1), dim3(1024), 0, st, A.S, A.n_total, A.ev_off, A.m_s, A.L,
-                       A.item_off, A.chunk_off, A.mu_off, A.a_off);
+    hipLaunchKernelGGL(small_setup, dim3(1), dim3(A.single ? 64 : 1024), 0, st, A.S, A.n_total, A.ev_off, A.m_s, A.L,
+                       A.item_off, A.chunk_off, A.mu_off, A.a_off, A.single ? (int64_t*)A.ev_off : (int64_t*)nullptr,
+                       (int32_t*)A.m_s, (double*)A.T_s, A.m1, A.T1);
     hipLaunchKernelGGL(small_agg<MP>, dim3((unsigned)blocks), dim3(256), 0, st, A.S, A.n_total, A.ev_off,
                        A.item_off, A.L,
                        A.t, A.marks, A.m_s, A.beta, A.item_pref, A.tile_agg, A.n_items_cap);
@@ -897,19 +972,23 @@ static hawkes_status run_small_mp(const SmallArgs& A, hipStream_t st) {
                            A.n_items_cap);
     }
     delete t4;
-    hipLaunchKernelGGL(small_reduce1, dim3((unsigned)A.n_chunks_cap), dim3(1024), 0, st, A.S, A.n_items_cap,
-                       A.item_off,
-                       A.chunk_off, A.part, PW, A.cpart, A.n_chunks_cap);
+    // up to 2048 items in all: one reduction of the items' partials (48
+    // sequences of 100 to 2000 events: 12 us for the two levels, 4.6 for one)
+    const bool one = A.n_items_cap <= 2048;
+    if (!one)
+        hipLaunchKernelGGL(small_reduce1, dim3((unsigned)A.n_chunks_cap), dim3(1024), 0, st, A.S, A.n_items_cap,
+                           A.item_off, A.chunk_off, A.part, PW, A.cpart, A.n_chunks_cap);
+    // few sequences: enough threads for their many chunks or items
+    const dim3 bd(A.S < 64 && (one || A.n_chunks_cap > 16) ? 1024 : 128);
+    auto last = [&](auto* kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)A.S), bd, 0, st, A.S, one ? A.n_items_cap : A.n_chunks_cap,
+                           one ? A.item_off : A.chunk_off, A.m_s, A.T_s, A.mu, A.beta, A.mu_off, A.a_off,
+                           one ? A.part : A.cpart, PW, A.loglik, A.g_mu, A.g_alpha, A.g_beta);
+    };
     if (A.grad)
-        hipLaunchKernelGGL((small_reduce2<MP, true>), dim3((unsigned)A.S), dim3(128), 0, st, A.S, A.n_chunks_cap,
-                           A.chunk_off,
-                           A.m_s, A.T_s, A.mu, A.beta, A.mu_off, A.a_off, A.cpart, PW, A.loglik, A.g_mu,
-                           A.g_alpha, A.g_beta);
+        last(small_reduce2<MP, true>);
     else
-        hipLaunchKernelGGL((small_reduce2<MP, false>), dim3((unsigned)A.S), dim3(128), 0, st, A.S, A.n_chunks_cap,
-                           A.chunk_off,
-                           A.m_s, A.T_s, A.mu, A.beta, A.mu_off, A.a_off, A.cpart, PW, A.loglik, A.g_mu,
-                           A.g_alpha, A.g_beta);
+        last(small_reduce2<MP, false>);
     return hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
