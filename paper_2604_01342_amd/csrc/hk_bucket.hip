@@ -1,4 +1,4 @@
-// Per-chunk partition of the events by node block (16, 64 or 128 nodes per block),
+// Per-chunk partition of the events by node block (16 or 128 nodes per block),
 // stable in event order: a counting sort in three steps.
 //   count    one wave per segment: events per (block, segment)
 //   scan     one workgroup per block: start of every (block, segment) run
@@ -11,7 +11,7 @@
 //            ballot per bit of the block number), plus the block's running
 //            count in LDS
 // Records: key = (event index in the chunk) << bs | (mark mod 2^bs) for blocks
-// of 2^bs nodes (bs = 4, 6 or 7), t (float64),
+// of 2^bs nodes (bs = 4 or 7), t (float64),
 // w = 1 / lambda (float32).  The dense-gradient kernels stream the records of
 // two blocks (the block of their rows and the block of their columns)
 // instead of filtering every event of the chunk.

@@ -7,8 +7,6 @@
 #ifndef HK_SEG
 #define HK_SEG 1024        // events per forward segment (one wave)
 #endif
-#define HK_RB 64           // targets per block of the per-target (adjoint) dense kernel
-#define HK_SLAB 64         // columns per dense-gradient block (one per lane)
 #define HK_NARROW_MAX_M 64   // nodes up to which one kernel takes the forward pass and the gradient
 #define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32
 #define HK_WIDE 60.0       // anchored-exponent limit inside one block of the dense gradient
@@ -27,8 +25,8 @@ struct LargeArgs {
     int64_t nchunks;
     int32_t nseg;         // segments per chunk
     int32_t ER;           // event ranges of the dense kernel per chunk
-    int32_t NB;           // node blocks of 64 (bucketing; columns of the dense kernels)
-    int32_t NBR, NBC;     // row and column blocks of the per-target dense kernel
+    int32_t seg;          // events per segment (HK_SEG; fewer with per-target decays and few events)
+    int32_t NB;           // per-target decays: node blocks of HK_PT_NB (partition and dense kernel)
     // shared decay: one kernel for few nodes (hk_narrow.hip), else hk_dense.hip
     bool narrow;
     int32_t BL;           // log2 of the events per block (6, 7 or 8)
@@ -122,6 +120,12 @@ struct ZeroList {
     }
 };
 
+// per-target decays: the shortest segment; the dense kernel's targets and
+// columns per block, and the fewest events for one of its waves
+#define HK_PT_SEG_MIN 256
+#define HK_PT_NB 128
+#define HK_PT_WAVE_EV 32
+#define HK_PT_SEG_ROWS (1 << 18)   // most segments times nodes of shortened segments (15 MB of maps and states)
 #define HK_SG 32           // segments per scan group
 #define HK_NBO_MAX 256     // node blocks the forward pass can count for the partition
 

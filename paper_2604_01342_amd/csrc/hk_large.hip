@@ -1018,12 +1018,22 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     // per-chunk buffers then scale with n for short sequences
     int lg = p->chunk_log2 ? p->chunk_log2 : 20;
     while (lg > 12 && ((int64_t)1 << (lg - 1)) >= p->n) --lg;
+    // a record of the per-target dense kernel: the event's index in the chunk
+    // beside the 7 bits of its node in the block
+    if (A.per_target && lg > 25) lg = 25;
     A.CH = (int64_t)1 << lg;
     A.nchunks = (A.n + A.CH - 1) / A.CH;
-    A.nseg = (int32_t)((A.CH + HK_SEG - 1) / HK_SEG);
-    A.NB = (A.M + 63) / 64;
+    // per-target decays, few events: shorter segments, about 1024 of them (one
+    // wave each in the aggregation and the forward pass; n = 2e5, M = 100:
+    // 54 + 31 us with 256 events, 173 + 96 with 1024)
+    A.seg = HK_SEG;
+    if (A.per_target && A.M <= 1024)
+        while (A.seg > HK_PT_SEG_MIN && (A.n < A.CH ? A.n : A.CH) < (int64_t)1024 * A.seg &&
+               (A.CH / A.seg) * 2 * A.M <= HK_PT_SEG_ROWS)
+            A.seg >>= 1;
+    A.nseg = (int32_t)((A.CH + A.seg - 1) / A.seg);
+    A.NB = (A.M + HK_PT_NB - 1) / HK_PT_NB;
     const hawkes_tuning tu = tuning_snapshot();
-    A.NBR = A.NBC = A.NB;
     // few nodes, one kernel: hk_narrow.hip, up to the 64 lanes of a wave.  The
     // forward pass, partition and dense kernels against it, n = 1e6: M = 16:
     // 87 + 14 + 86 us against 44; M = 50, dense rows: 119 + 13 + 119 against 95
@@ -1039,15 +1049,12 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         }
         A.ER = er < 1 ? 1 : (int32_t)er;
     } else if (A.per_target) {
-        // event ranges per chunk for the per-target dense kernel: a power of
-        // two so that the ranges map onto the 8 XCDs evenly, about 2048
-        // workgroups in total
-        const int64_t want = (2048 + (int64_t)A.NB * A.NB - 1) / ((int64_t)A.NB * A.NB);
-        int32_t er = 1;
-        while (er < want) er <<= 1;
-        while (er > A.nseg && er > 1) er >>= 1;
-        A.ER = er;
-        A.DRB = 6;
+        // event ranges of the per-target dense kernel: as many workgroups as
+        // run at once (one a CU), and some events for every wave
+        const int64_t ev = A.n < A.CH ? A.n : A.CH;
+        int64_t er = 256 / ((int64_t)A.NB * A.NB);
+        if (er > ev / (HK_PT_WAVE_EV * 16)) er = ev / (HK_PT_WAVE_EV * 16);
+        A.ER = er < 1 ? 1 : (int32_t)er;
         A.BL = 6;
     } else {
         // dense dL/dalpha (hk_dense.hip).  Events per block: the pair terms

@@ -51,15 +51,14 @@ namespace hk {
 // at M = 4096)
 #define PT_CHAIN_EV 2048
 #define PT_STAGE_CHAIN 960
-// waves per workgroup of the dense kernel: eight share the 64 x 64 LDS tile,
-// three workgroups a CU (measured at c5: 3.36 ms per launch against 4.01 with
-// four waves, 4.19 with seven, 4.49 with nine)
-#ifndef HK_DWP
-#define HK_DWP 8
-#endif
-// largest beta_max (t_first - t_last) of a dense-kernel window that takes the
-// merged path: e^64 and e^-64 stay well inside float32's range
-#define HK_PT_MERGE_SPAN 64.0
+// the dense kernel's targets per lane and waves per workgroup: 16 waves share
+// the 128 x 128 LDS tile, one workgroup a CU
+#define PT_DR 2
+#define PT_DW 16
+// P(x) = (1 - e^{-x}) / x on [0, 1/4]: the polynomial through its values at
+// the five Chebyshev points of the interval (within 2.5e-9 of it everywhere)
+__device__ constexpr double PT_EXPC[5] = {0.999999997575856, -0.49999951482099725, 0.1666510820661627,
+                                          -0.04149065410430236, 0.007513606221824206};
 
 // Inclusive prefix sum over the 64 lanes of a wave on the vector ALU (DPP):
 // shifts within rows of 16 lanes (row_shr 1, 2, 4, 8), then each row's total
@@ -115,7 +114,7 @@ __device__ __forceinline__ double pt_rdl_d(double v, int k) {
 // of the two variants launched for a chunk, the one that does not apply
 // returns at once.
 template <bool FAR, int STG>
-__global__ __launch_bounds__(64) void pt_seg_agg(int64_t c0, int64_t c1, int32_t M, double T,
+__global__ __launch_bounds__(64) void pt_seg_agg(int64_t c0, int64_t c1, int32_t seg, int32_t M, double T,
                                                  const double* __restrict__ t, const int32_t* __restrict__ marks,
                                                  const float* __restrict__ beta, const int32_t* __restrict__ csc_ptr,
                                                  const int2* __restrict__ csc_cv, const float* __restrict__ csc_b,
@@ -130,8 +129,8 @@ __global__ __launch_bounds__(64) void pt_seg_agg(int64_t c0, int64_t c1, int32_t
     double* ev_t = lds + (FAR ? 2 : 3) * M;    // [64]
     int4* stg = (int4*)(ev_t + 64);            // [STG] (target, alpha, event, beta)
     const int32_t s = blockIdx.x;
-    const int64_t a = c0 + (int64_t)s * HK_SEG;
-    const int64_t b = a + HK_SEG < c1 ? a + HK_SEG : c1;
+    const int64_t a = c0 + (int64_t)s * seg;
+    const int64_t b = a + seg < c1 ? a + seg : c1;
     const int lane = threadIdx.x;
     for (int32_t q = lane; q < M; q += 64) {
         aR[q] = 0.0;
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(512) void pt_chain_fold(int64_t c0, int64_t c1, int
 // Events tied in time keep index order (a later event sees an earlier one's
 // push at distance 0), as in the recurrence.
 template <bool GRAD, bool INTENS>
-__global__ __launch_bounds__(64) void pt_forward(int64_t c0, int64_t c1, int32_t M, double T,
+__global__ __launch_bounds__(64) void pt_forward(int64_t c0, int64_t c1, int32_t seg, int32_t M, double T,
                                                  const double* __restrict__ t, const int32_t* __restrict__ marks,
                                                  const float* __restrict__ mu, const float* __restrict__ beta,
                                                  const int32_t* __restrict__ csc_ptr,
@@ -509,8 +508,8 @@ __global__ __launch_bounds__(64) void pt_forward(int64_t c0, int64_t c1, int32_t
     uint8_t* tev = (uint8_t*)(stg + PT_STAGE);
     const int32_t s = blockIdx.x;
     const int lane = threadIdx.x;
-    const int64_t a = c0 + (int64_t)s * HK_SEG;
-    const int64_t b = a + HK_SEG < c1 ? a + HK_SEG : c1;
+    const int64_t a = c0 + (int64_t)s * seg;
+    const int64_t b = a + seg < c1 ? a + seg : c1;
     const double tref = a > 0 ? t[a - 1] : t[a];
     const double* cs = carry_seg + (int64_t)s * 2 * M;
     // Anchored records when the segment's span allows, beta_max (t_last -
@@ -836,8 +835,10 @@ __global__ __launch_bounds__(1024) void pt_eb_reduce(int32_t nseg, int32_t M, co
     const int32_t per = (nseg + 15) / 16;
     const int32_t s0 = sl * per, s1 = s0 + per < nseg ? s0 + per : nseg;
     double v = 0.0;
-    if (p < M)
+    if (p < M) {
+#pragma unroll 16
         for (int32_t s = s0; s < s1; ++s) v += ebseg[(int64_t)s * M + p];
+    }
     part[sl][lane] = v;
     __syncthreads();
     if (sl == 0 && p < M) {
@@ -851,21 +852,21 @@ __global__ __launch_bounds__(1024) void pt_eb_reduce(int32_t nseg, int32_t M, co
 // time of segment s's first event; for s == nseg, the time the chunk's right
 // carry refers to (the next chunk's first event, or T after the last chunk)
 __device__ __forceinline__ double seg_first_time(const double* __restrict__ t, int64_t c0, int64_t c1, int64_t n,
-                                                 int32_t nseg, int32_t s, double T) {
+                                                 int32_t seg, int32_t nseg, int32_t s, double T) {
     if (s >= nseg) return c1 < n ? t[c1] : T;
-    return t[c0 + (int64_t)s * HK_SEG];
+    return t[c0 + (int64_t)s * seg];
 }
 
 // aggA[s][p] = sum_{i in segment s, m_i = p} w_i e^{-beta_p (t_i - t_first(s))}
 // (wv indexed from the chunk start c0); one wave per segment, LDS aA[M]
-__global__ __launch_bounds__(64) void pt_rev_agg(int64_t c0, int64_t c1, int32_t M, const double* __restrict__ t,
+__global__ __launch_bounds__(64) void pt_rev_agg(int64_t c0, int64_t c1, int32_t seg, int32_t M, const double* __restrict__ t,
                                                  const int32_t* __restrict__ marks, const float* __restrict__ beta,
                                                  const float* __restrict__ wv, double* __restrict__ aggA) {
     extern __shared__ double lds[];
     double* aA = lds;
     const int32_t s = blockIdx.x;
-    const int64_t a = c0 + (int64_t)s * HK_SEG;
-    const int64_t b = a + HK_SEG < c1 ? a + HK_SEG : c1;
+    const int64_t a = c0 + (int64_t)s * seg;
+    const int64_t b = a + seg < c1 ? a + seg : c1;
     const int lane = threadIdx.x;
     for (int32_t q = lane; q < M; q += 64) aA[q] = 0.0;
     __syncthreads();
@@ -889,7 +890,7 @@ __global__ __launch_bounds__(64) void pt_rev_agg(int64_t c0, int64_t c1, int32_t
 //   apply   1 thread per (segment, target): add the group's right carry
 // rcarry_seg[s][p] ends as A_p at t_first(s) from the events of segment s on
 // (this and later chunks, plus the seed).
-__global__ void pt_rscan_local(int64_t c0, int64_t c1, int64_t n, double T, int32_t nseg, int32_t M,
+__global__ __launch_bounds__(256) void pt_rscan_local(int64_t c0, int64_t c1, int64_t n, double T, int32_t seg, int32_t nseg, int32_t M,
                                const double* __restrict__ t, const float* __restrict__ beta,
                                const double* __restrict__ aggA, double* __restrict__ rcarry_seg,
                                double* __restrict__ rgagg) {
@@ -899,17 +900,26 @@ __global__ void pt_rscan_local(int64_t c0, int64_t c1, int64_t n, double T, int3
     const int32_t g = (int32_t)(gid / M), p = (int32_t)(gid % M);
     const int32_t s0 = g * HK_SG, s1 = s0 + HK_SG < nseg ? s0 + HK_SG : nseg;
     const double bp = (double)beta[p];
-    double A = 0.0, tn = seg_first_time(t, c0, c1, n, nseg, s1, T);
-    for (int32_t s = s1 - 1; s >= s0; --s) {
-        const double ts = seg_first_time(t, c0, c1, n, nseg, s, T);
-        A = __builtin_fma(exp(-bp * (tn - ts)), A, aggA[(int64_t)s * M + p]);
-        rcarry_seg[(int64_t)s * M + p] = A;
-        tn = ts;
+    // a group's loads and decays before the chain (one multiply-add a segment)
+    double ag[HK_SG], ex[HK_SG], ts[HK_SG + 1];
+#pragma unroll
+    for (int u = 0; u <= HK_SG; ++u) ts[u] = seg_first_time(t, c0, c1, n, seg, nseg, s0 + u < s1 ? s0 + u : s1, T);
+#pragma unroll
+    for (int u = 0; u < HK_SG; ++u) ag[u] = aggA[(int64_t)(s0 + u < s1 ? s0 + u : s1 - 1) * M + p];
+#pragma unroll
+    for (int u = 0; u < HK_SG; ++u) ex[u] = exp_f64(-bp * (ts[u + 1] - ts[u]));
+    double A = 0.0;
+#pragma unroll
+    for (int u = HK_SG - 1; u >= 0; --u) {
+        if (s0 + u < s1) {
+            A = __builtin_fma(ex[u], A, ag[u]);
+            rcarry_seg[(int64_t)(s0 + u) * M + p] = A;
+        }
     }
     rgagg[(int64_t)g * M + p] = A;
 }
 
-__global__ void pt_rscan_groups(int64_t c0, int64_t c1, int64_t n, double T, int32_t nseg, int32_t M,
+__global__ __launch_bounds__(256) void pt_rscan_groups(int64_t c0, int64_t c1, int64_t n, double T, int32_t seg, int32_t nseg, int32_t M,
                                 const double* __restrict__ t, const float* __restrict__ beta,
                                 const double* __restrict__ rgagg, double* __restrict__ rgcarry,
                                 double* __restrict__ achunk) {
@@ -917,17 +927,33 @@ __global__ void pt_rscan_groups(int64_t c0, int64_t c1, int64_t n, double T, int
     if (p >= M) return;
     const int32_t ngr = (nseg + HK_SG - 1) / HK_SG;
     const double bp = (double)beta[p];
-    double A = achunk[p], tn = seg_first_time(t, c0, c1, n, nseg, nseg, T);
-    for (int32_t g = ngr - 1; g >= 0; --g) {
-        rgcarry[(int64_t)g * M + p] = A;
-        const double ts = seg_first_time(t, c0, c1, n, nseg, g * HK_SG, T);
-        A = __builtin_fma(exp(-bp * (tn - ts)), A, rgagg[(int64_t)g * M + p]);
-        tn = ts;
+    // 16 groups at a time, their loads and decays before the chain
+    constexpr int PF = 16;
+    double A = achunk[p];
+    for (int32_t gb = ngr; gb > 0; gb -= PF) {
+        double ag[PF], ex[PF], ts[PF + 1];
+#pragma unroll
+        for (int u = 0; u <= PF; ++u) {
+            const int32_t g = gb - u > 0 ? gb - u : 0;
+            ts[u] = seg_first_time(t, c0, c1, n, seg, nseg, g == ngr ? nseg : g * HK_SG, T);
+        }
+#pragma unroll
+        for (int u = 0; u < PF; ++u) ag[u] = rgagg[(int64_t)(gb - 1 - u > 0 ? gb - 1 - u : 0) * M + p];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bp * (ts[u] - ts[u + 1]));
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int32_t g = gb - 1 - u;
+            if (g >= 0) {
+                rgcarry[(int64_t)g * M + p] = A;
+                A = __builtin_fma(ex[u], A, ag[u]);
+            }
+        }
     }
     achunk[p] = A;
 }
 
-__global__ void pt_rscan_apply(int64_t c0, int64_t c1, int64_t n, double T, int32_t nseg, int32_t M,
+__global__ void pt_rscan_apply(int64_t c0, int64_t c1, int64_t n, double T, int32_t seg, int32_t nseg, int32_t M,
                                const double* __restrict__ t, const float* __restrict__ beta,
                                const double* __restrict__ rgcarry, double* __restrict__ rcarry_seg) {
     const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -935,191 +961,242 @@ __global__ void pt_rscan_apply(int64_t c0, int64_t c1, int64_t n, double T, int3
     const int32_t s = (int32_t)(gid / M), p = (int32_t)(gid % M);
     const int32_t g = s / HK_SG;
     const int32_t s1 = (g + 1) * HK_SG < nseg ? (g + 1) * HK_SG : nseg;
-    const double te = seg_first_time(t, c0, c1, n, nseg, s1, T);
-    const double ts = seg_first_time(t, c0, c1, n, nseg, s, T);
-    rcarry_seg[(int64_t)s * M + p] += exp(-(double)beta[p] * (te - ts)) * rgcarry[(int64_t)g * M + p];
+    const double te = seg_first_time(t, c0, c1, n, seg, nseg, s1, T);
+    const double ts = seg_first_time(t, c0, c1, n, seg, nseg, s, T);
+    rcarry_seg[(int64_t)s * M + p] += exp_f64(-(double)beta[p] * (te - ts)) * rgcarry[(int64_t)g * M + p];
+}
+
+// First record of [lo, hi) (positions in the records of one node block, at most
+// HK_SEG of them, in event order) whose event index is e or later; the wave
+// probes 64 records, then the up to 16 between two of them.
+__device__ __forceinline__ int64_t rec_lower_bound(const uint32_t* __restrict__ key, int64_t lo, int64_t hi, int bs,
+                                                   int32_t e) {
+    const int lane = threadIdx.x & 63;
+    const int32_t step = (int32_t)((hi - lo + 63) >> 6);
+    const int64_t i = lo + (int64_t)lane * step;
+    const int below = __builtin_popcountll(__ballot(i < hi && (int32_t)(key[i < hi ? i : lo] >> bs) < e));
+    if (hi <= lo || below == 0) return lo;
+    const int64_t base = lo + (int64_t)(below - 1) * step;
+    const int64_t j = base + lane;
+    const bool in = lane < step && j < hi;
+    return base + __builtin_popcountll(__ballot(in && (int32_t)(key[in ? j : lo] >> bs) < e));
 }
 
 // Dense adjoint kernel.  Block = (target block rb, source block sb, event
-// range er), HK_DWP waves, each over its share of the range's segments; lane
-// l owns target p = r0 + l and beta_p A_p (float64), A_p the adjoint state
-// from the events after the current read position, kept at an anchor time.
-// The block reads only the bucketed records of its two node blocks ("own":
-// targets in rb; "slab": sources in sb), from the end of the range
-// backwards, merged by event index in windows of up to 64 + 64 records (the
-// window starts where either list's 64th record from the end is).  Per
-// window: A moves to the window's latest event time tw; every slab event k
-// adds beta_p A_p(t_k) to column m_k of the block: the state decayed to t_k
-// plus the window's own-target events after k.  Three forms, by the window's
-// largest decay exponent beta_max (tw - t_last): short windows (<= 0.5) and
-// windows past HK_PT_MERGE_SPAN add the own events' part pairwise (one
-// masked ds_add per slab event) and then enter the own events into A at the
-// window's earliest time; the windows between enter them into A in event
-// order inside the slab loop.  G is kept in LDS column-major (stride 65
-// against bank conflicts).  Blocks with sb == 0 also sum w_i per target,
-// blocks with rb == 0 count the events per source.
-__global__ __launch_bounds__(64 * HK_DWP) void pt_dense(int64_t c0, int64_t c1, int64_t n, double T, int32_t M, int32_t NB,
-                                               int32_t ER, int32_t segs_per_range, int32_t nseg,
-                                               const double* __restrict__ t, const float* __restrict__ beta,
-                                               const double* __restrict__ rcarry_seg,
-                                               const double* __restrict__ rgcarry,
-                                               const int32_t* __restrict__ bk_off,
-                                               const int32_t* __restrict__ bk_base,
-                                               const uint32_t* __restrict__ bk_key, const double* __restrict__ bk_t,
-                                               const float* __restrict__ bk_w, double* __restrict__ gpart,
-                                               double* __restrict__ spart, double* __restrict__ npart) {
-    __shared__ double G[HK_SLAB * 65];   // shared by the group's waves
-    __shared__ double ALs[HK_DWP][64], SLs[HK_DWP][64], NLs[HK_DWP][64];
-    __shared__ float BL[64];
+// range er), blocks of 128 nodes, 16 waves, each over its share of the range's
+// events; lane l owns the targets p = r0 + l and r0 + l + 64 and their beta_p
+// A_p (float64), A_p the adjoint state from the events after the current read
+// position.  A wave starts from the state at the next segment's first event,
+// which it moves to its own share's end over the own targets' events between
+// (at most a segment's).  The block reads only the bucketed records of its two
+// node blocks ("own": targets in rb; "slab": sources in sb), from the end of
+// the range backwards, merged by event index in windows of up to 64 + 64
+// records (the window starts where either list's 64th record from the end
+// is).  A goes through the window's slab events in turn: e^{-beta_p d} over
+// the step d from the one before, the own-target events passed on the way
+// (each with its decay to the slab event on its target's lane), then beta_p
+// A_p to column m_k of G.  The decay is a polynomial in float64 with the
+// lane's coefficients, the step halved until it applies and the result squared
+// as often: no range of steps needs another form, and A carries no float32
+// decay.  G is kept in LDS column-major (stride 129 against bank conflicts).
+// Blocks with sb == 0 also sum w_i per target, blocks with rb == 0 count the
+// events per source.
+//
+// Bound by the vector ALU: 25 instructions per slab event and 128 targets (12
+// decays, 4 for the own event joined meanwhile, 4 for the event's step and
+// column, 5 of the window's share); the two LDS adds are hidden.
+// M = 4096, 2^20 events: 2.40 ms a launch; 2.88 with blocks of 64 targets and
+// columns (twice the own events and window set-ups per slab event and target)
+// and float32 exponentials with their correction terms; 2.72 without the
+// rotating priority.  M = 100, 2e5 events: 35 us, 204 with one wave for every
+// segment of 1024 events.
+__global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, int64_t n, double T, int32_t M, int32_t NB,
+                                                   int32_t ER, int32_t seg, int32_t nseg, int32_t nsegb,
+                                                   const double* __restrict__ t, const float* __restrict__ beta,
+                                                   const double* __restrict__ rcarry_seg,
+                                                   const double* __restrict__ rgcarry,
+                                                   const int32_t* __restrict__ bk_off,
+                                                   const int32_t* __restrict__ bk_base,
+                                                   const uint32_t* __restrict__ bk_key, const double* __restrict__ bk_t,
+                                                   const float* __restrict__ bk_w, double* __restrict__ gpart,
+                                                   double* __restrict__ spart, double* __restrict__ npart) {
+    constexpr int R = PT_DR, W = PT_DW, B = 64 * R, BS = 7, GS = B + 1;
+    static_assert(B == 1 << BS && B == HK_PT_NB, "node blocks of the partition");
+    extern __shared__ double lds[];
+    double* G = lds;                               // [B columns][GS], shared by the waves
+    float* BL = (float*)(G + B * GS + W * B);      // [B]
+    uint32_t* NL = (uint32_t*)(BL + B);            // [B] events per source
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
-    double* AL = ALs[wv];
-    double* SL = SLs[wv];
-    double* NL = NLs[wv];
-    AL[lane] = 0.0;
-    SL[lane] = 0.0;
-    NL[lane] = 0.0;
-    const int32_t blk = blockIdx.x;
-    const int32_t nbb = NB * NB;
-    int32_t er, local;
-    if (ER >= 8) {
-        const int32_t slot = blk >> 3;
-        er = (slot / nbb) * 8 + (blk & 7);
-        local = slot % nbb;
-    } else {
-        const int32_t per = 8 / ER, x = blk & 7;
-        er = x / per;
-        local = (blk >> 3) * per + x % per;
-        if (local >= nbb) return;
-    }
-    if (er >= ER) return;
-    const int32_t sb = local % NB;
-    const int32_t rb = local / NB;
-    const int32_t r0 = rb * HK_RB, s0 = sb * HK_SLAB;
-    const int32_t gA = er * segs_per_range;
-    if (gA >= nseg) return;
-    const int32_t gB = gA + segs_per_range < nseg ? gA + segs_per_range : nseg;
-    // this wave's share of the range's segments (possibly none)
-    const int32_t sA = gA + (wv * (gB - gA)) / HK_DWP;
-    const int32_t sB = gA + ((wv + 1) * (gB - gA)) / HK_DWP;
-    const int32_t p = r0 + lane;
-    const bool pv = p < M;
-    BL[lane] = pv ? beta[p] : 0.0f;
-    double* gp = gpart + (int64_t)er * M * M;
-    {
-        // lanes over the block's columns (coalesced rows of gpart)
-        const int32_t col = s0 + lane;
-        const int32_t cc = col < M ? col : M - 1;
-        for (int rg = wv * 16; rg < HK_RB; rg += 16 * HK_DWP) {
-            double v[16];
+    double* AL = G + B * GS + wv * B;              // [B] this wave's
+    // work items range-major, an eighth of them in a row to each XCD: the
+    // blocks of a range share its records in the XCD's L2
+    const int32_t nbb = NB * NB, items = nbb * ER, per = (items + 7) >> 3;
+    const int32_t slot = (int32_t)(blockIdx.x >> 3), item = (int32_t)(blockIdx.x & 7) * per + slot;
+    if (slot >= per || item >= items) return;
+    const int32_t er = item / nbb, local = item % nbb;
+    const int32_t sb = local % NB, rb = local / NB;
+    const int32_t r0 = rb * B, s0 = sb * B;
+    // this wave's share of the chunk's events, [e0, e1)
+    const int64_t nev = c1 - c0, shares = (int64_t)ER * W;
+    const int32_t e0 = (int32_t)(nev * ((int64_t)er * W + wv) / shares);
+    const int32_t e1 = (int32_t)(nev * ((int64_t)er * W + wv + 1) / shares);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
+    for (int r = 0; r < R; ++r) AL[lane + 64 * r] = 0.0;
+    double ca[5][R], sl_sum[R], Ab[R];   // e^{-beta_p d}'s coefficients; sums of w; beta_p A_p at the time tau
+    double bmax = 0.0;                 // largest decay of the block's targets
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int32_t p = r0 + lane + 64 * r;
+        const float b = p < M ? beta[p] : 0.0f;
+        if (wv == 0) {
+            BL[lane + 64 * r] = b;
+            NL[lane + 64 * r] = 0;
+        }
+        double bq = 1.0;
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            bq *= (double)b;
+            ca[u][r] = -PT_EXPC[u] * bq;
+        }
+        bmax = (double)b > bmax ? (double)b : bmax;
+        sl_sum[r] = 0.0;
+        Ab[r] = 0.0;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(bmax, off, 64);
+        bmax = o > bmax ? o : bmax;
+    }
+    double* gp = gpart + (int64_t)er * M * M;
+    // lanes over the block's columns (coalesced rows of gpart)
+#pragma unroll
+    for (int cg = 0; cg < R; ++cg) {
+        const int32_t col = s0 + 64 * cg + lane;
+        const int32_t cc = col < M ? col : M - 1;
+        for (int rg = wv * 8; rg < B; rg += 8 * W) {
+            double v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
                 const int32_t row = r0 + rg + j;
                 const int32_t rr = row < M ? row : M - 1;
                 v[j] = gp[(int64_t)rr * M + cc];
             }
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
+            for (int j = 0; j < 8; ++j) {
                 const int32_t row = r0 + rg + j;
-                G[lane * 65 + rg + j] = (row < M && col < M) ? v[j] : 0.0;
+                G[(64 * cg + lane) * GS + rg + j] = (row < M && col < M) ? v[j] : 0.0;
             }
         }
     }
-    const double bp = pv ? (double)beta[p] : 0.0;
-    const double bp2 = bp * HK_LOG2E;                      // beta_p log2(e)
-    const float bpl = (float)bp2;
-    const float bpl_lo = (float)(bp2 - (double)bpl);       // bp2 = bpl + bpl_lo to ~2^-48
-    // largest decay of the block's targets
-    double bmax = bp;
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(bmax, off, 64);
-        bmax = o > bmax ? o : bmax;
-    }
-    // adjoint state from the events after the range (and the seed) at tau
-    const bool at_end = sB >= nseg;
-    double tau = seg_first_time(t, c0, c1, n, nseg, at_end ? nseg : sB, T);
-    double Ab = 0.0;   // beta_p A_p at the anchor tau
-    if (pv) {
-        const int32_t ngr = (nseg + HK_SG - 1) / HK_SG;
-        Ab = bp * (at_end ? rgcarry[(int64_t)(ngr - 1) * M + p] : rcarry_seg[(int64_t)sB * M + p]);
-    }
-    RecStream<true> O, S;
-    O.init(bk_key, bk_t, bk_w, (int64_t)bk_base[rb] + bk_off[(int64_t)rb * (nseg + 1) + sA],
-           (int64_t)bk_base[rb] + bk_off[(int64_t)rb * (nseg + 1) + sB]);
-    S.init(bk_key, bk_t, bk_w, (int64_t)bk_base[sb] + bk_off[(int64_t)sb * (nseg + 1) + sA],
-           (int64_t)bk_base[sb] + bk_off[(int64_t)sb * (nseg + 1) + sB]);
-    O.settle();
-    S.settle();
     __syncthreads();
-    for (;;) {
-        if (sA >= sB) break;
-        const int64_t ao = O.avail(), as = S.avail();
-        if (ao <= 0 && as <= 0) break;
-        const int io = (int)(O.ck >> 6), is = (int)(S.ck >> 6);
-        const int lim_o = ao > 64 ? rl_i(io, 63) : -1;
-        const int lim_s = as > 64 ? rl_i(is, 63) : -1;
-        const int lo = lim_o > lim_s ? lim_o : lim_s;
-        const bool own = lane < ao && io >= lo;
-        const bool sl = lane < as && is >= lo;
-        const int no = __builtin_popcountll(__ballot(own));
-        const int ns = __builtin_popcountll(__ballot(sl));
-        double tw = -1e300, tl = 1e300;
-        if (no) { tw = rl_d(O.ct, 0); tl = rl_d(O.ct, no - 1); }
-        if (ns) {
-            const double a0 = rl_d(S.ct, 0), a1 = rl_d(S.ct, ns - 1);
-            tw = a0 > tw ? a0 : tw;
-            tl = a1 < tl ? a1 : tl;
+    if (e0 < e1) {
+        // adjoint state from the events after the share, at tau: of the next
+        // segment's start (or the chunk's end), moved to the first event
+        // after the share
+        const int32_t sn = (e1 + seg - 1) / seg;
+        const bool at_end = sn >= nseg;
+        const int32_t es = at_end ? (int32_t)nev : sn * seg;
+        double tau = seg_first_time(t, c0, c1, n, seg, nseg, at_end ? nseg : sn, T);
+        const int32_t ngr = (nseg + HK_SG - 1) / HK_SG;
+        const double* A0 = at_end ? rgcarry + (int64_t)(ngr - 1) * M : rcarry_seg + (int64_t)sn * M;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t p = r0 + lane + 64 * r;
+            if (p < M) Ab[r] = (double)beta[p] * A0[p];
         }
-        Ab *= (double)exp2_f64arg((tw - tau) * bp2);
-        const int pi = (int)(O.ck & 63u);
-        const double bo = (double)BL[pi];
-        const double bo2 = bo * HK_LOG2E;
-        const float bol = (float)bo2;
-        const double wi = (double)O.cw;
-        bool merged = false;
-        if (bmax * (tw - tl) <= 0.5) {
-            // short window: every decay exponent is at most 0.5 in magnitude,
-            // so float32 arguments cost at most 2.5e-7 relative and the
-            // hardware exp2 applies directly.  The time differences are taken
-            // in float64 once per lane (slab lane k: tw - t_k; own lane:
-            // t_i - tw, folded into the exponent's constant), then each slab
-            // event's offset and key are broadcast by one readlane apiece.
-            // Lanes without an own event add 0 to their own column slot (a
-            // finite 0: their exponent constant is 0, not a stale record's).
-            const float dks = (float)(tw - S.ct);
-            const float c2 = own ? -bol * (float)(O.ct - tw) : 0.0f;
-            const int pa = own ? pi : lane;
-            const double bA = Ab, bw = own ? bo * wi : 0.0;
-            const int keys = (int)S.ck;
-            for (int k = 0; k < ns; ++k) {
-                const uint32_t key = (uint32_t)rl_i(keys, k);
-                const float dk = rl_f(dks, k);
-                const int qoff = (int)(key & 63u) * 65;
-                const float e1 = __builtin_amdgcn_exp2f(-bpl * dk);
-                const float e2 = __builtin_amdgcn_exp2f(__builtin_fmaf(-bol, dk, c2));
-                atomicAdd(&G[qoff + lane], bA * (double)e1);
-                // own event later than slab event k (both lists newest first)
-                atomicAdd(&G[qoff + pa], bw * (double)(io > (int)(key >> 6) ? e2 : 0.0f));
+        auto pos = [&](int32_t blk, int32_t e) -> int64_t {
+            const int32_t* off = bk_off + (int64_t)blk * (nsegb + 1);
+            if (e >= nev) return bk_base[blk] + (int64_t)off[nsegb];
+            const int32_t s = e / HK_SEG;
+            return rec_lower_bound(bk_key, bk_base[blk] + (int64_t)off[s], bk_base[blk] + (int64_t)off[s + 1], BS, e);
+        };
+        const int64_t oA = pos(rb, e0), oB = pos(rb, e1), sA = pos(sb, e0), sB = pos(sb, e1);
+        if (e1 < es) {
+            const double tx = t[c0 + e1];
+            const int64_t oE = pos(rb, es);
+            for (int64_t i0 = oB; i0 < oE; i0 += 64) {
+                const int64_t i = i0 + lane;
+                if (i < oE) {
+                    const int pi = (int)(bk_key[i] & (B - 1));
+                    const double bo = (double)BL[pi];
+                    atomicAdd(&AL[pi], bo * (double)bk_w[i] * exp_f64(bo * (tx - bk_t[i])));
+                }
             }
-        } else if (bmax * (tw - tl) <= HK_PT_MERGE_SPAN) {
-            // long window, merged: A is moved to the anchor tw, and the
-            // window's own events enter it in event order between the slab
-            // events (newest first), each as beta_{m_i} w_i e^{beta_{m_i}
-            // (tw - t_i)} on its target's lane, so every slab event needs one decay
-            // e^{-beta_p (tw - t_k)} per lane and one ds_add.  The span bound
-            // keeps both factors inside float32's exponent range.  The decay's
-            // exponent is split in two floats (tw - t_k = dh + dl, beta_p
-            // log2(e) = bpl + bpl_lo, and the product's rounding error by an
-            // fma), so 2^-x = 2^-xh (1 - xl ln2) is as accurate as the
-            // hardware exp2 at any x in range.
-            merged = true;
-            const double dd = tw - S.ct;
-            const float dh = (float)dd, dl0 = (float)(dd - (double)dh);
-            // per slab lane k: the own events later than it, the first dcnt of
-            // the own list (both lists newest first: a binary search over the
-            // own indices), and with its column in the 13 low mantissa bits of
-            // the low part of its offset (dl changes by at most 2^-10 of
-            // itself, 2^-34 of the offset), so that one readlane gives all
+            lds_wait();   // the wave's adds land before its reads
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                Ab[r] = __builtin_fma(Ab[r], exp_f64((double)BL[lane + 64 * r] * (tx - tau)), AL[lane + 64 * r]);
+                AL[lane + 64 * r] = 0.0;
+            }
+            lds_wait();
+            tau = tx;
+        }
+        // d over a power of two 2^*h, beta_max d / 2^*h < 1/4
+        auto halved = [&](double d, int* h) -> double {
+            int e = __builtin_amdgcn_frexp_exp(bmax * d) + 2;
+            e = e < 0 ? 0 : (e > 100 ? 100 : e);
+            *h = e;
+            return __builtin_ldexp(d, -e);
+        };
+        // A over a step of 2^h d: e^{-x} = 1 - x P(x) to the power 2^h, x =
+        // beta d in [0, 1/4]
+        auto decay = [&](double d, int h) {
+            double E[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                double v = __builtin_fma(d, ca[4][r], ca[3][r]);
+                v = __builtin_fma(d, v, ca[2][r]);
+                v = __builtin_fma(d, v, ca[1][r]);
+                v = __builtin_fma(d, v, ca[0][r]);
+                E[r] = __builtin_fma(d, v, 1.0);
+            }
+            for (; h > 0; --h)
+#pragma unroll
+                for (int r = 0; r < R; ++r) E[r] *= E[r];
+#pragma unroll
+            for (int r = 0; r < R; ++r) Ab[r] *= E[r];
+        };
+        RecStream<true> O, S;
+        O.init(bk_key, bk_t, bk_w, oA, oB);
+        S.init(bk_key, bk_t, bk_w, sA, sB);
+        O.settle();
+        S.settle();
+        int rot = wv >> 2;
+        for (;;) {
+            // of a SIMD's waves the oldest would issue first throughout and
+            // the youngest finish a third later; the priority goes round
+            rot = (rot + 1) & 3;
+            if (rot == 0)
+                __builtin_amdgcn_s_setprio(0);
+            else if (rot == 1)
+                __builtin_amdgcn_s_setprio(1);
+            else if (rot == 2)
+                __builtin_amdgcn_s_setprio(2);
+            else
+                __builtin_amdgcn_s_setprio(3);
+            const int64_t ao = O.avail(), as = S.avail();
+            if (ao <= 0 && as <= 0) break;
+            const int io = (int)(O.ck >> BS), is = (int)(S.ck >> BS);
+            const int lim_o = ao > 64 ? rl_i(io, 63) : -1;
+            const int lim_s = as > 64 ? rl_i(is, 63) : -1;
+            const int lo = lim_o > lim_s ? lim_o : lim_s;
+            const bool own = lane < ao && io >= lo;
+            const bool sl = lane < as && is >= lo;
+            const int no = __builtin_popcountll(__ballot(own));
+            const int ns = __builtin_popcountll(__ballot(sl));
+            const double tl = no && ns ? fmin(rl_d(O.ct, no - 1), rl_d(S.ct, ns - 1))
+                                       : (no ? rl_d(O.ct, no - 1) : rl_d(S.ct, ns - 1));
+            const int pi = (int)(O.ck & (B - 1));
+            const double wi = (double)O.cw;
+            // per slab lane: the step to its time from the one before it (the
+            // first: from tau), halved until beta_max times it is below 1/4
+            double dv = __shfl_up(S.ct, 1, 64);
+            dv = lane == 0 ? tau : dv;
+            int hv;
+            dv = halved(dv - S.ct, &hv);
+            // and its column and the own events later than it: the first
+            // dcnt of the own list (both lists newest first: a binary search
+            // over the own indices)
             int dcnt = 0;
 #pragma unroll
             for (int step = 64; step >= 1; step >>= 1) {
@@ -1127,93 +1204,101 @@ __global__ __launch_bounds__(64 * HK_DWP) void pt_dense(int64_t c0, int64_t c1, 
                 const int ov = __shfl(io, probe & 63, 64);
                 if (probe < no && ov > is) dcnt += step;
             }
-            const float dl = __int_as_float((__float_as_int(dl0) & ~8191) | (dcnt << 6) | (int)(S.ck & 63u));
-            // the own event's target lane rides in the 6 low mantissa bits of
-            // its weight (a change of at most 2^-46 relative), so one pair
-            // of readlanes gives both
-            const double fo = own ? bo * wi * (double)exp2_f64arg((tw - O.ct) * bo2) : 0.0;
-            const double fop = __longlong_as_double((__double_as_longlong(fo) & ~63ll) | (long long)pi);
+            const int kbv = (hv << 16) | (dcnt << 8) | (int)(S.ck & (B - 1));
+            // per own lane: beta w e^{-beta (t_i - t)} at the time t of the
+            // first slab event before it (no such event: tl)
+            int kj = 0;
+#pragma unroll
+            for (int step = 64; step >= 1; step >>= 1) {
+                const int probe = kj + step - 1;
+                const int sv = __shfl(is, probe & 63, 64);
+                if (probe < ns && sv >= io) kj += step;
+            }
+            const double tk = __shfl(S.ct, kj & 63, 64);
+            const double bo = (double)BL[pi];
+            const double fo = own ? bo * wi * exp_f64(-bo * (O.ct - (kj < ns ? tk : tl))) : 0.0;
+            // the own event's target rides in the low mantissa bits of its
+            // weight (a change of at most 2^-45 relative), so one pair of
+            // readlanes gives both
+            const double fop = __longlong_as_double((__double_as_longlong(fo) & ~(long long)(B - 1)) | (long long)pi);
             int j = 0;
-            for (int k = 0; k < ns; ++k) {
-                const float xl0 = rl_f(dl, k);
-                const int kb = __float_as_int(xl0);
-                // own events later than slab event k (the first dk of the
-                // list, newest first) join A before it
-                const int dk = (kb >> 6) & 127;
+            // own events up to dk join A
+            auto join = [&](int dk) {
                 for (; j < dk; ++j) {
                     const double f = rl_d(fop, j);
-                    if (lane == (int)(__double_as_longlong(f) & 63)) {
-                        Ab += f;
-                        // keeps the add under the lane's exec mask (else the
-                        // compiler adds on every lane and selects: two more
-                        // vector instructions per own event)
-                        __asm__ volatile("" : "+v"(Ab));
+                    const int q = (int)(__double_as_longlong(f) & (B - 1));
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if (R > 1 && (q >> 6) != r) continue;
+                        if (lane == (q & 63)) {
+                            Ab[r] += f;
+                            // keeps the add under the lane's exec mask (else the
+                            // compiler adds on every lane and selects: two more
+                            // vector instructions per own event)
+                            __asm__ volatile("" : "+v"(Ab[r]));
+                        }
                     }
                 }
-                const float xh0 = rl_f(dh, k);
-                const float xh = bpl * xh0;
-                const float xl = __builtin_fmaf(bpl, xl0, __builtin_fmaf(bpl_lo, xh0, __builtin_fmaf(bpl, xh0, -xh)));
-                const float e0 = __builtin_amdgcn_exp2f(-xh);
-                const float e = __builtin_fmaf(e0, xl * -0.69314718f, e0);
-                atomicAdd(&G[(kb & 63) * 65 + lane], Ab * (double)e);
-            }
-            // own events older than every slab event of the window
-            for (; j < no; ++j) {
-                const double f = rl_d(fop, j);
-                if (lane == (int)(__double_as_longlong(f) & 63)) {
-                    Ab += f;
-                    __asm__ volatile("" : "+v"(Ab));
-                }
-            }
-        } else {
+            };
             for (int k = 0; k < ns; ++k) {
-                const int qoff = (int)(rl_i((int)S.ck, k) & 63) * 65;
-                const double tk = rl_d(S.ct, k);
-                const int ik = rl_i(is, k);
-                atomicAdd(&G[qoff + lane], Ab * (double)exp2_f64arg((tk - tw) * bp2));
-                if (own && io > ik) atomicAdd(&G[qoff + pi], bo * wi * (double)exp2_f64arg((tk - O.ct) * bo2));
+                const int kb = rl_i(kbv, k);
+                decay(rl_d(dv, k), kb >> 16);
+                join((kb >> 8) & 255);
+                double* g = &G[(kb & (B - 1)) * GS + lane];
+#pragma unroll
+                for (int r = 0; r < R; ++r) atomicAdd(g + 64 * r, Ab[r]);
             }
-        }
-        if (sb == 0 && own) atomicAdd(&SL[pi], wi);
-        if (rb == 0 && sl) atomicAdd(&NL[S.ck & 63u], 1.0);
-        if (merged) {
-            tau = tw;   // A already holds the window's own events, anchored at tw
-        } else {
-            if (own) atomicAdd(&AL[pi], bo * wi * (double)exp2_f64arg((tl - O.ct) * bo2));
-            // AL is this wave's; its atomics land before the read
-            lds_wait();
-            Ab = __builtin_fma(Ab, (double)exp2_f64arg((tl - tw) * bp2), AL[lane]);
-            __builtin_amdgcn_wave_barrier();
-            AL[lane] = 0.0;
-            __builtin_amdgcn_wave_barrier();
+            // to the window's earliest time, and the own events older than
+            // every slab event
+            int hl;
+            const double dlast = halved((ns ? rl_d(S.ct, ns - 1) : tau) - tl, &hl);
+            decay(dlast, __builtin_amdgcn_readfirstlane(hl));
+            join(no);
             tau = tl;
+            if (sb == 0) {
+                if (own) atomicAdd(&AL[pi], wi);
+                lds_wait();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    sl_sum[r] += AL[lane + 64 * r];
+                    AL[lane + 64 * r] = 0.0;
+                }
+                lds_wait();
+            }
+            if (rb == 0 && sl) atomicAdd(&NL[S.ck & (B - 1)], 1u);
+            O.shift(no);
+            S.shift(ns);
+            O.refill();
+            S.refill();
         }
-        O.shift(no);
-        S.shift(ns);
-        O.refill();
-        S.refill();
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) AL[lane + 64 * r] = sl_sum[r];
     __syncthreads();
-    {
-        const int32_t col = s0 + lane;
+#pragma unroll
+    for (int cg = 0; cg < R; ++cg) {
+        const int32_t col = s0 + 64 * cg + lane;
         if (col < M) {
-#pragma unroll 16
-            for (int r = wv; r < HK_RB; r += HK_DWP) {
+#pragma unroll 8
+            for (int r = wv; r < B; r += W) {
                 const int32_t row = r0 + r;
-                if (row < M) gp[(int64_t)row * M + col] = G[lane * 65 + r];
+                if (row < M) gp[(int64_t)row * M + col] = G[(64 * cg + lane) * GS + r];
             }
         }
     }
-    if (wv != 0) return;
-    // the waves' sums, in wave order
-    double sl = 0.0, nl = 0.0;
-    for (int v = 0; v < HK_DWP; ++v) {
-        sl += SLs[v][lane];
-        nl += NLs[v][lane];
+    // the waves' sums of w, in wave order, and the counts
+    for (int x = threadIdx.x; x < B; x += 64 * W) {
+        if (sb == 0 && r0 + x < M) {
+            double v = 0.0;
+            for (int w = 0; w < W; ++w) v += G[B * GS + w * B + x];
+            spart[(int64_t)er * M + r0 + x] += v;
+        }
+        if (rb == 0 && s0 + x < M) npart[(int64_t)er * M + s0 + x] += (double)NL[x];
     }
-    if (sb == 0 && pv) spart[(int64_t)er * M + p] += sl;
-    if (rb == 0 && s0 + lane < M) npart[(int64_t)er * M + s0 + lane] += nl;
 }
+
+static constexpr size_t PT_DENSE_LDS = (size_t)(HK_PT_NB * (HK_PT_NB + 1) + PT_DW * HK_PT_NB) * sizeof(double) +
+                                       (size_t)HK_PT_NB * (sizeof(float) + sizeof(uint32_t));
 
 // ------------------------------------------------------------------ host
 hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
@@ -1232,7 +1317,8 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
         allow_lds((const void*)pt_forward<false, true>, lds_fwd) != HAWKES_OK ||
         allow_lds((const void*)pt_forward<false, false>, lds_fwd) != HAWKES_OK ||
         allow_lds((const void*)pt_rev_agg, lds_rev) != HAWKES_OK ||
-        allow_lds((const void*)pt_chain_part<PT_STAGE_CHAIN>, lds_chain) != HAWKES_OK)
+        allow_lds((const void*)pt_chain_part<PT_STAGE_CHAIN>, lds_chain) != HAWKES_OK ||
+        allow_lds((const void*)pt_dense, PT_DENSE_LDS) != HAWKES_OK)
         return HAWKES_EUNSUPPORTED;
     // the gradient's two checkpoint levels hold at most HK_PTCK^2 chunks
     if (A.grad && A.pt_ckr > HK_PTCK) return HAWKES_EUNSUPPORTED;
@@ -1257,7 +1343,7 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
     auto chunk_range = [&](int64_t ch, int64_t& c0, int64_t& c1) -> int32_t {
         c0 = ch * A.CH;
         c1 = c0 + A.CH < A.n ? c0 + A.CH : A.n;
-        return (int32_t)((c1 - c0 + HK_SEG - 1) / HK_SEG);
+        return (int32_t)((c1 - c0 + A.seg - 1) / A.seg);
     };
     // segment maps and their scan: carry_seg of the chunk from A.carry (its
     // start state), which moves to the chunk's end
@@ -1266,11 +1352,11 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
             TimedScope ts(2, st);
             hipLaunchKernelGGL(pt_near, dim3(1), dim3(64), 0, st, c1, A.T, A.t, flags);
             const int32_t* nearf = reinterpret_cast<const int32_t*>(flags) + 1;
-            hipLaunchKernelGGL((pt_seg_agg<true, PT_STAGE_CHAIN>), dim3(nseg), dim3(64), lds_agg_far, st, c0, c1, M,
+            hipLaunchKernelGGL((pt_seg_agg<true, PT_STAGE_CHAIN>), dim3(nseg), dim3(64), lds_agg_far, st, c0, c1, A.seg, M,
                                A.T, A.t, A.marks, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.agg, A.seg_span, A.ebseg,
                                A.seg_part, nearf);
-            hipLaunchKernelGGL((pt_seg_agg<false, PT_STAGE_AGG>), dim3(nseg), dim3(64), lds_agg, st, c0, c1, M, A.T,
-                               A.t, A.marks, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.agg, A.seg_span, A.ebseg,
+            hipLaunchKernelGGL((pt_seg_agg<false, PT_STAGE_AGG>), dim3(nseg), dim3(64), lds_agg, st, c0, c1, A.seg, M,
+                               A.T, A.t, A.marks, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.agg, A.seg_span, A.ebseg,
                                A.seg_part, nearf);
         }
         TimedScope ts(3, st);
@@ -1293,15 +1379,15 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
         {
             TimedScope ts(1, st);
             if (A.grad)
-                hipLaunchKernelGGL((pt_forward<true, false>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, M, A.T, A.t,
-                                   A.marks, A.mu, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.carry_seg, A.seg_part,
+                hipLaunchKernelGGL((pt_forward<true, false>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, A.seg, M, A.T,
+                                   A.t, A.marks, A.mu, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.carry_seg, A.seg_part,
                                    A.ebseg, A.wv, (float*)nullptr);
             else if (A.lambda_out)
-                hipLaunchKernelGGL((pt_forward<false, true>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, M, A.T, A.t,
-                                   A.marks, A.mu, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.carry_seg, A.seg_part,
+                hipLaunchKernelGGL((pt_forward<false, true>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, A.seg, M, A.T,
+                                   A.t, A.marks, A.mu, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.carry_seg, A.seg_part,
                                    A.ebseg, (float*)nullptr, A.lambda_out);
             else
-                hipLaunchKernelGGL((pt_forward<false, false>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, M, A.T,
+                hipLaunchKernelGGL((pt_forward<false, false>), dim3(nseg), dim3(64), lds_fwd, st, c0, c1, A.seg, M, A.T,
                                    A.t, A.marks, A.mu, A.beta, A.csc_ptr, A.csc_cv, csc_b, A.carry_seg,
                                    A.seg_part, A.ebseg, (float*)nullptr, (float*)nullptr);
         }
@@ -1361,30 +1447,28 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
                 agg_scan(c0, c1, nseg);
                 forward(c0, c1, nseg);
                 const int32_t ngr = (nseg + HK_SG - 1) / HK_SG;
+                const int32_t nsegb = (int32_t)((c1 - c0 + HK_SEG - 1) / HK_SEG);   // of the partition
                 const int64_t nloc = (int64_t)ngr * M, napp = (int64_t)nseg * M;
                 {
                     TimedScope ts(3, st);
-                    hipLaunchKernelGGL(pt_rev_agg, dim3(nseg), dim3(64), lds_rev, st, c0, c1, M, A.t, A.marks,
+                    hipLaunchKernelGGL(pt_rev_agg, dim3(nseg), dim3(64), lds_rev, st, c0, c1, A.seg, M, A.t, A.marks,
                                        A.beta, A.wv, A.aggA);
                     hipLaunchKernelGGL(pt_rscan_local, dim3((unsigned)((nloc + 255) / 256)), dim3(256), 0, st, c0,
-                                       c1, A.n, A.T, nseg, M, A.t, A.beta, A.aggA, A.rcarry_seg, A.rgagg);
-                    hipLaunchKernelGGL(pt_rscan_groups, dim3(gM), dim3(256), 0, st, c0, c1, A.n, A.T, nseg, M, A.t,
+                                       c1, A.n, A.T, A.seg, nseg, M, A.t, A.beta, A.aggA, A.rcarry_seg, A.rgagg);
+                    hipLaunchKernelGGL(pt_rscan_groups, dim3(gM), dim3(256), 0, st, c0, c1, A.n, A.T, A.seg, nseg, M, A.t,
                                        A.beta, A.rgagg, A.rgcarry, A.achunk);
                     hipLaunchKernelGGL(pt_rscan_apply, dim3((unsigned)((napp + 255) / 256)), dim3(256), 0, st, c0,
-                                       c1, A.n, A.T, nseg, M, A.t, A.beta, A.rgcarry, A.rcarry_seg);
+                                       c1, A.n, A.T, A.seg, nseg, M, A.t, A.beta, A.rgcarry, A.rcarry_seg);
                 }
                 {
                     TimedScope tb(6, st);
-                    bucket_chunk(A, c0, c1, nseg, A.wv, 6, st);
+                    bucket_chunk(A, c0, c1, nsegb, A.wv, 7, st);
                 }
-                const int32_t spr = (nseg + A.ER - 1) / A.ER;
-                const int32_t nbb = A.NB * A.NB;
-                const unsigned nblk = A.ER >= 8 ? (unsigned)(nbb * ((A.ER + 7) / 8) * 8)
-                                                : (unsigned)(((nbb + 8 / A.ER - 1) / (8 / A.ER)) * 8);
+                const unsigned nblk = (unsigned)((A.NB * A.NB * A.ER + 7) / 8 * 8);
                 TimedScope ts(0, st);
-                hipLaunchKernelGGL(pt_dense, dim3(nblk), dim3(64 * HK_DWP), 0, st, c0, c1, A.n, A.T, M, A.NB, A.ER,
-                                   spr, nseg, A.t, A.beta, A.rcarry_seg, A.rgcarry, A.bk_off, A.bk_base, A.bk_key,
-                                   A.bk_t, A.bk_w, A.gpart, A.spart, A.cpart_);
+                hipLaunchKernelGGL(pt_dense, dim3(nblk), dim3(64 * PT_DW), PT_DENSE_LDS, st, c0, c1, A.n, A.T, M, A.NB,
+                                   A.ER, A.seg, nseg, nsegb, A.t, A.beta, A.rcarry_seg, A.rgcarry, A.bk_off,
+                                   A.bk_base, A.bk_key, A.bk_t, A.bk_w, A.gpart, A.spart, A.cpart_);
             }
         }
     }
