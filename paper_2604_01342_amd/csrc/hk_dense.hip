@@ -23,9 +23,10 @@
 // is visited once, not once per column block, and every record lane of a
 // visit but the last group's adds.
 // Measured per chunk of 2^20 events at M = 1000: dense_prep 32 us and
-// dense_tiles 171 us (pair terms alone 116, the product alone 124 with the
-// pair waves' loads), against 27 + 304 us (and 12 for the partition's scatter,
-// now in dense_prep) for tiles of 32 x 256 nodes walking windows of 128 column
+// dense_tiles 158 us (at equal issue priority of its waves 171, of which the
+// pair terms alone 116 and the product alone, with the pair waves' loads,
+// 124), against 27 + 304 us (and 12 for the partition's scatter, now in
+// dense_prep) for tiles of 32 x 256 nodes walking windows of 128 column
 // records; pair terms and product as two kernels: 120 + 89 us.
 #include "hk_device.h"
 #include "hk_large.h"
@@ -281,6 +282,11 @@ __device__ __forceinline__ int32_t xcd_item(int32_t total) {
 // U[k + l / 16][row l mod 16], K[k + l / 16][column l mod 16]; result register
 // r is row 4 (l / 16) + r (float32) or 4 r + l / 16 (float64), column l mod 16.
 //
+// Issue priority: the product waves last (their products fill the pair waves'
+// gaps), a SIMD's pair waves in turn.  At equal priority the oldest wave goes
+// first: the product ended at 72% and the pair waves at 82 to 100% of the
+// launch (M = 1000, 2^20 events: 174 us; 158 now).
+//
 // PAIRS = false: the sums per node only.  MC: several column blocks.
 #define HK_TW 16      // waves
 #define HK_TGW 4      // of them on the product
@@ -448,6 +454,7 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
     __syncthreads();
     if (wv < HK_TGW) {
         if constexpr (PAIRS) {
+            __builtin_amdgcn_s_setprio(0);
             // this wave's column groups of 64 (float32) or 32 (float64)
             constexpr int GC = 256 / sizeof(RT);
             const int nm = (((CW + GC - 1) / GC) - wv + HK_TGW - 1) / HK_TGW;
@@ -469,6 +476,7 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
         const double bet = (double)beta[0];
         const double bl2 = bet * HK_LOG2E;
         const int pw = wv - HK_TGW;
+        int rot = pw >> 2;
         const int32_t* off = bo_off + (int64_t)rb * (nseg + 1);
         const int32_t ob = bo_base[rb];
         // this wave's blocks and own records
@@ -541,6 +549,14 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
                     own_sums(oc, oL);
                     continue;
                 }
+                // a SIMD's three pair waves take turns at the front
+                rot = rot == 2 ? 0 : rot + 1;
+                if (rot == 0)
+                    __builtin_amdgcn_s_setprio(1);
+                else if (rot == 1)
+                    __builtin_amdgcn_s_setprio(2);
+                else
+                    __builtin_amdgcn_s_setprio(3);
                 blk_load(rn, blk + 1);
                 const bool w = __builtin_amdgcn_readfirstlane(rc.wide) != 0;
                 int pl[NG];

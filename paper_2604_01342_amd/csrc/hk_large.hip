@@ -330,12 +330,17 @@ __global__ void large_scan_apply(int32_t nseg, int32_t M, const double* __restri
 }
 
 // ------------------------------------------------------------------ forward
-#ifndef HK_FWW
-#define HK_FWW 2   // waves per forward-pass segment
-#endif
-#ifndef HK_FW
-#define HK_FW 16   // nonzeros of an event's row of alpha loaded one batch ahead
-#endif
+// Four waves per segment, in the 128 registers that let four of them share a
+// SIMD (a chunk of 2^20 events has 1024 segments: with two waves each, and 190
+// registers, two were on a SIMD and the pass waited more than half its time).
+// Us a launch, two / four waves: M = 1000, 1e6 events, gradient 57 / 51,
+// log-likelihood 51 / 43; M = 251, 3e5 events 52 / 40; M = 100, 1e6 events,
+// intensities 56 / 47.  Two waves where four waves' sums and the records pass
+// the LDS (M > HK_FW4_MAX_M).
+#define HK_FW4_MAX_M 6400
+// nonzeros of an event's row of alpha loaded one batch ahead (more of them
+// with four waves cost registers: 24 spilled with 16)
+constexpr int fwd_ahead(int nw) { return nw == 4 ? 8 : 16; }
 // RM (several decay kernels): the pass runs once per kernel and writes, per
 // event, R = alpha_{m_i,:} . K(t_i) to rk and (GRAD) D = alpha_{m_i,:} . J(t_i)
 // to dk instead of forming lambda; large_combine then sums the kernels.
@@ -361,7 +366,7 @@ __device__ __forceinline__ double recip(double x) {
 }
 
 template <bool GRAD, bool INTENS, bool SUPP, int NW, bool RM = false>
-__global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1, int32_t M, double T,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 4 : 1))) void large_forward(int64_t c0, int64_t c1, int32_t M, double T,
                                                     const double* __restrict__ t, const int32_t* __restrict__ marks,
                                                     const float* __restrict__ mu, const float* __restrict__ beta,
                                                     const int4* __restrict__ node_info,
@@ -383,6 +388,7 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
     // NW waves share a segment's events; wave wv takes the aligned pairs of
     // nonzeros wv, wv + NW, ... of each event's row of alpha
     const int wv = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    constexpr int WE = NW == 4 ? 1 : NW - 1;
     static_assert(!SUPP || NW == 1, "the support-restricted sums are formed by one wave");
     static_assert(!(RM && (SUPP || INTENS)), "per-kernel sums only");
     const int64_t a = c0 + (int64_t)s * HK_SEG;
@@ -399,9 +405,7 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
     // time rtau[q] and is decayed on use.
     const bool anch = bet * (t[b - 1] - tref) <= 600.0;
     // [M] the lazy records' times, in the segment's slot of a global scratch
-    // buffer (24 bytes of LDS per node instead of 32: M up to 6741).  Three
-    // waves per SIMD (168 registers, six workgroups per CU at M = 1000) made
-    // the pass slower at c4's shape: 0.674 against 0.591 ms per step
+    // buffer (24 bytes of LDS per node instead of 32: M up to 6741)
     double* rtau = X.rtau + (int64_t)s * 2 * M;
     const double* cs = carry_seg + (int64_t)s * 2 * M;
     const double* gc = X.gcarry ? X.gcarry + (int64_t)(s / HK_SG) * 2 * M : nullptr;
@@ -433,7 +437,7 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
     // one 16-byte load; the first and last pair may hold a neighbour row's
     // entry, which is skipped): these gathers hit a different cache line per
     // lane, so the number of load instructions, not bytes, sets their cost.
-    constexpr int FW = HK_FW;          // nonzeros loaded ahead per event
+    constexpr int FW = fwd_ahead(NW);  // nonzeros loaded ahead per event
     constexpr int FP = FW / (2 * NW);  // pairs of them loaded by this wave
     static_assert(FP >= 1 && FP * 2 * NW == FW, "look-ahead must be whole pairs per wave");
     const int4* __restrict__ cv4 = reinterpret_cast<const int4*>(csr_cv);
@@ -462,22 +466,20 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
     int4 pr0[FP];
     ld_row(n0, pr0);
     for (int64_t base = a; base < b; base += 64) {
+        // the waves with the batch's serial work go first
+        if (NW > 1 && (wv == 0 || wv == NW - 1)) __builtin_amdgcn_s_setprio(2);
         const int64_t i = base + lane;
         const bool valid = i < b;
         const double ti = valid ? t0 : 0.0;
         const int mi = valid ? m0 : 0;
         const int4 ni = n0;
         // loads for the batches ahead
-        double t3;
-        int m3;
-        ld_tm(base + 192, t3, m3);
         const int4 n2 = node_info[m2];
         int4 pr1[FP];
         ld_row(n1, pr1);
         const double ui = ti - tref;
-        // the last wave takes the batch's compensator terms (they do not need
-        // the sums), beside the first wave's logarithm and reciprocal (one
-        // wave: the first does all)
+        // after the sums: the first wave the logarithm and reciprocal, wave WE
+        // the compensator terms, wave WC the records (one wave: all of it)
         constexpr int WC = NW - 1;
         double eti = 0.0;   // e^{beta u_i} (anchored records; the first wave)
         if (wv == 0) {
@@ -598,12 +600,15 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
                 }
             }
         }
+        double t3;
+        int m3;
+        ld_tm(base + 192, t3, m3);
         // e^{-beta u_i} (anchored records) as the reciprocal of e^{beta u_i}
         // (1 <= e^{beta u_i} <= e^600): a division instead of a second
         // exponential on the first wave, whose share of the batch is the longer
         double ei = 1.0;
         if (anch && valid && wv == 0) ei = recip(eti);
-        if (!RM && valid && wv == WC) {
+        if (!RM && valid && wv == WE) {
             // compensator terms of the event's node (eq. 2) and their
             // beta-derivative part (eq. 10)
             const double x = bet * (T - ti);
@@ -659,7 +664,7 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
             }
         }
         if (!RM && GRAD && valid && wv == 0) wchunk[i - c0] = (float)w;
-        // the records take the batch's events (the last wave, beside the
+        // the records take the batch's events (wave WC, beside the
         // first wave's work above: nothing there reads the records), then the
         // batch's masks are cleared
         if (anch) {
@@ -720,8 +725,8 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
         for (int32_t k = threadIdx.x; k < X.nbo; k += 64 * NW) X.bcnt[(int64_t)k * gridDim.x + s] = lcnt[k];
     }
     // deterministic wave reductions of the float64 partials: the log-sum and
-    // dL/dbeta part in the first wave, the compensator sums in the last
-    if (RM || (wv != 0 && wv != NW - 1)) return;
+    // dL/dbeta part in the first wave, the compensator sums in wave WE
+    if (RM || (wv != 0 && wv != WE)) return;
     for (int off = 32; off > 0; off >>= 1) {
         logsum += __shfl_down(logsum, off, 64);
         comp += __shfl_down(comp, off, 64);
@@ -736,7 +741,7 @@ __global__ __launch_bounds__(64 * NW) void large_forward(int64_t c0, int64_t c1,
             o[0] += logsum;
             o[3] += gb;
         }
-        if (wv == NW - 1) {
+        if (wv == WE) {
             o[1] += comp;
             o[2] += Esum;
         }
@@ -1255,6 +1260,22 @@ static void dense_zero(const LargeArgs& A, ZeroList& Z) {
     Z.add(A.cpart_, (int64_t)A.K * A.NSP * A.M);
 }
 
+// launches the forward pass's form of four waves per segment, or of two
+template <bool GRAD, bool INTENS, bool RM>
+struct Fwd {
+    static const void* kernel(int32_t M) {
+        return M <= HK_FW4_MAX_M ? (const void*)large_forward<GRAD, INTENS, false, 4, RM>
+                                 : (const void*)large_forward<GRAD, INTENS, false, 2, RM>;
+    }
+    template <typename... Args>
+    static void launch(int32_t M, int32_t nseg, size_t lds, hipStream_t st, Args... args) {
+        if (M <= HK_FW4_MAX_M)
+            hipLaunchKernelGGL((large_forward<GRAD, INTENS, false, 4, RM>), dim3(nseg), dim3(256), lds, st, args...);
+        else
+            hipLaunchKernelGGL((large_forward<GRAD, INTENS, false, 2, RM>), dim3(nseg), dim3(128), lds, st, args...);
+    }
+};
+
 static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
     const int32_t M = A.M, K = A.K;
     const int64_t MM = (int64_t)M * M;
@@ -1262,8 +1283,8 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
     const size_t lds_agg = (size_t)2 * M * sizeof(double);
     const size_t lds_fwd = (size_t)M * (sizeof(uint64_t) + 2 * sizeof(double));
     if (allow_lds((const void*)large_seg_agg, lds_agg) != HAWKES_OK ||
-        allow_lds((const void*)large_forward<true, false, false, HK_FWW, true>, lds_fwd) != HAWKES_OK ||
-        allow_lds((const void*)large_forward<false, false, false, HK_FWW, true>, lds_fwd) != HAWKES_OK)
+        allow_lds(Fwd<true, false, true>::kernel(M), lds_fwd) != HAWKES_OK ||
+        allow_lds(Fwd<false, false, true>::kernel(M), lds_fwd) != HAWKES_OK)
         return HAWKES_EUNSUPPORTED;
     if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const int32_t W = 2 + 2 * K;
@@ -1308,14 +1329,12 @@ static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
             }
             TimedScope ts(1, st);
             if (A.grad)
-                hipLaunchKernelGGL((large_forward<true, false, false, HK_FWW, true>), dim3(nseg), dim3(64 * HK_FWW),
-                                   lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu, B.beta,
+                Fwd<true, false, true>::launch(M, nseg, lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu, B.beta,
                                    A.node_info + (int64_t)k * M, A.csr_cv + k * cv_stride(MM), B.carry_seg,
                                    A.seg_part, A.wchunk, (float*)nullptr, (double*)nullptr, 0,
                                    A.rk + (int64_t)k * A.CH, A.dk + (int64_t)k * A.CH, Xm);
             else
-                hipLaunchKernelGGL((large_forward<false, false, false, HK_FWW, true>), dim3(nseg), dim3(64 * HK_FWW),
-                                   lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu, B.beta,
+                Fwd<false, false, true>::launch(M, nseg, lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu, B.beta,
                                    A.node_info + (int64_t)k * M, A.csr_cv + k * cv_stride(MM), B.carry_seg,
                                    A.seg_part, A.wchunk, (float*)nullptr, (double*)nullptr, 0,
                                    A.rk + (int64_t)k * A.CH, (double*)nullptr, Xm);
@@ -1390,10 +1409,10 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     const size_t lds_agg = (size_t)2 * M * sizeof(double);
     const size_t lds_fwd = (size_t)M * (sizeof(uint64_t) + 2 * sizeof(double));
     if (allow_lds((const void*)large_seg_agg, lds_agg) != HAWKES_OK ||
-        allow_lds((const void*)large_forward<true, false, false, HK_FWW>, lds_fwd) != HAWKES_OK ||
+        allow_lds(Fwd<true, false, false>::kernel(M), lds_fwd) != HAWKES_OK ||
         allow_lds((const void*)large_forward<true, false, true, 1>, lds_fwd) != HAWKES_OK ||
-        allow_lds((const void*)large_forward<false, true, false, HK_FWW>, lds_fwd) != HAWKES_OK ||
-        allow_lds((const void*)large_forward<false, false, false, HK_FWW>, lds_fwd) != HAWKES_OK)
+        allow_lds(Fwd<false, true, false>::kernel(M), lds_fwd) != HAWKES_OK ||
+        allow_lds(Fwd<false, false, false>::kernel(M), lds_fwd) != HAWKES_OK)
         return HAWKES_EUNSUPPORTED;
     if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const bool sup = A.grad && A.support;
@@ -1417,7 +1436,7 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     size_t lds_fwdc = lds_fwd;   // the gradient's forward pass, with the partition counts if they fit
     if (A.grad && A.NBO <= HK_NBO_MAX) {
         const void* kf = sup ? (const void*)large_forward<true, false, true, 1>
-                             : (const void*)large_forward<true, false, false, HK_FWW>;
+                             : Fwd<true, false, false>::kernel(M);
         if (allow_lds(kf, lds_fwd + (size_t)A.NBO * sizeof(int32_t)) == HAWKES_OK) {
             X.bcnt = A.bo_cnt;
             lds_fwdc = lds_fwd + (size_t)A.NBO * sizeof(int32_t);
@@ -1454,21 +1473,18 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
                                    A.carry_seg, A.seg_part, A.wchunk, (float*)nullptr, A.gsup, ncopy - 1,
                                    (double*)nullptr, (double*)nullptr, X);
             else if (A.grad)
-                hipLaunchKernelGGL((large_forward<true, false, false, HK_FWW>), dim3(nseg), dim3(64 * HK_FWW), lds_fwdc,
-                                   st, c0, c1,
-                                   M, A.T, A.t, A.marks, A.mu, A.beta, A.node_info, A.csr_cv,
+                Fwd<true, false, false>::launch(M, nseg, lds_fwdc, st, c0, c1, M, A.T, A.t, A.marks, A.mu,
+                                   A.beta, A.node_info, A.csr_cv,
                                    A.carry_seg, A.seg_part, A.wchunk, (float*)nullptr, (double*)nullptr, 0,
                                    (double*)nullptr, (double*)nullptr, X);
             else if (A.lambda_out)
-                hipLaunchKernelGGL((large_forward<false, true, false, HK_FWW>), dim3(nseg), dim3(64 * HK_FWW), lds_fwd,
-                                   st, c0, c1,
-                                   M, A.T, A.t, A.marks, A.mu, A.beta, A.node_info, A.csr_cv,
+                Fwd<false, true, false>::launch(M, nseg, lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu,
+                                   A.beta, A.node_info, A.csr_cv,
                                    A.carry_seg, A.seg_part, A.wchunk, A.lambda_out, (double*)nullptr, 0,
                                    (double*)nullptr, (double*)nullptr, X);
             else
-                hipLaunchKernelGGL((large_forward<false, false, false, HK_FWW>), dim3(nseg), dim3(64 * HK_FWW), lds_fwd,
-                                   st, c0, c1,
-                                   M, A.T, A.t, A.marks, A.mu, A.beta, A.node_info, A.csr_cv,
+                Fwd<false, false, false>::launch(M, nseg, lds_fwd, st, c0, c1, M, A.T, A.t, A.marks, A.mu,
+                                   A.beta, A.node_info, A.csr_cv,
                                    A.carry_seg, A.seg_part, A.wchunk, (float*)nullptr, (double*)nullptr, 0,
                                    (double*)nullptr, (double*)nullptr, X);
         }
