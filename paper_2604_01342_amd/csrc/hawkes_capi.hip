@@ -37,11 +37,12 @@ size_t small_layout(SmallArgs& A, int32_t S, int64_t n_total, int32_t max_m, boo
     // and more partials to add.  Us a call with 16 / 32 / 64 / 128 events, one
     // sequence: 1e6 events, M = 1: 184 / 119 / 102 / 125, M = 5: 232 / 151 /
     // 119 / 138; 1e5, M = 8: 63 / 63 / 89 / 126; batches: 2.9e6 events in 200:
-    // 114 / 92 / 94 / 109; 6.3e7 in 4096 with 256 / 512 / 1024: 1240 / 1198 /
-    // 1184.
+    // 114 / 92 / 94 / 109; 5e6 in 500, M = 8, 32 / 64 / 128: 182 / 162 / 178;
+    // 2e7 in 2000, M = 3, 64 / 128 / 256: 357 / 335 / 356; 6.3e7 in 4096 with
+    // 256 / 512 / 1024: 1240 / 1198 / 1184.
     int64_t L = 16;
-    const int64_t target_items = single ? 24576 : 131072;
-    while (L < 4096 && n_total / L > target_items) L <<= 1;
+    const int64_t target_items = single ? 24576 : 163840;
+    while (L < 4096 && n_total / L > (single || L >= 64 ? target_items : 98304)) L <<= 1;
     if (n_total / L > target_items) L = (n_total + target_items - 1) / target_items;
     // a tuned item length replaces this one unless it makes more items than the
     // workspace is meant for

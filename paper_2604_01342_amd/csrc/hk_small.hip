@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256) void small_compute(int32_t S, int64_t n_total,
 // over the group (a butterfly, identical in every lane); the block's
 // logarithms are taken afterwards, again one event per lane.  The per-node
 // sums of the event's node (w, 1 - e^{-beta (T - t)} and (T - t)
-// e^{-beta (T - t)}) go to the item's LDS row by the event's lane (LDS
+// e^{-beta (T - t)}) go to the item's LDS row, one of them to a lane (LDS
 // atomics: no selects over the nodes), and the compensator and its
 // beta-derivative come from them at the item's end, weighted by the column
 // sums of alpha.  The lanes' scalar partials are summed in lane order.
@@ -608,7 +608,16 @@ __device__ __forceinline__ double pair_dpp(double x) {
     return __hiloint2double(hi, lo);
 }
 
-template <int MP, int LPI>
+// Lane i's double of the group of LPI (2 or 4) lanes, for each of them
+template <int LPI>
+__device__ __forceinline__ double grp_bcast(double x, int i) {
+    if constexpr (LPI == 2)
+        return i == 0 ? pair_dpp<0xA0>(x) : pair_dpp<0xF5>(x);
+    else
+        return i == 0 ? pair_dpp<0x00>(x) : i == 1 ? pair_dpp<0x55>(x) : i == 2 ? pair_dpp<0xAA>(x) : pair_dpp<0xFF>(x);
+}
+
+template <int MP, int LPI, bool GL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void small_compute_c(int32_t S, int64_t n_total, const int64_t* __restrict__ ev_off,
                                                        const int64_t* __restrict__ item_off, int32_t L,
                                                        const double* __restrict__ t,
@@ -694,11 +703,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         }
     }
     double lsum = 0.0, gbs = 0.0;
-    double Gc[MP][CL];
+    // the item's dL/dalpha block: registers, or (GL) LDS, lane c's column u of
+    // row p at [u][p][c] (consecutive items 4 banks of 8 bytes apart)
+    constexpr int GR = MP * LPI;
+    __shared__ double GLs[GL ? 4 * IPW : 1][GL ? CL * GR + 4 : 1];
+    double* gl = GLs[GL ? (threadIdx.x >> 6) * IPW + lane / LPI : 0];
+    double Gc[GL ? 1 : MP][CL];
 #pragma unroll
     for (int u = 0; u < CL; ++u)
 #pragma unroll
-        for (int r = 0; r < MP; ++r) Gc[r][u] = 0.0;
+        for (int r = 0; r < MP; ++r) {
+            if constexpr (GL)
+                gl[u * GR + r * LPI + c] = 0.0;
+            else
+                Gc[r][u] = 0.0;
+        }
     int mp = -1;
     // the items' events in rounds of NB, staged through LDS (coalesced
     // loads), the next round's loads in flight while one is processed
@@ -743,14 +762,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         for (int j = 0; j < NB; ++j) {
             if (e0 + j >= inf.b) break;
             double sj, ex;
-            if (LPI == 2) {
-                sj = j % 2 == 0 ? pair_dpp<0xA0>(so[j / 2]) : pair_dpp<0xF5>(so[j / 2]);
-                ex = j % 2 == 0 ? pair_dpp<0xA0>(xo[j / 2]) : pair_dpp<0xF5>(xo[j / 2]);
-            } else {
-                const int src = g0 + j % LPI;
-                sj = __shfl(so[j / LPI], src, 64);
-                ex = __shfl(xo[j / LPI], src, 64);
-            }
+            sj = grp_bcast<LPI>(so[j / LPI], j % LPI);
+            ex = grp_bcast<LPI>(xo[j / LPI], j % LPI);
             const double te = tv[j];
             const double d = te - tp;
             const int p = clamp_mark(mv[j], M);
@@ -764,15 +777,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
                 R = __builtin_fma(a, K[u], R);
                 Dd = __builtin_fma(a, J[u], Dd);
             }
-            if (LPI == 2) {
-                R += pair_dpp<0xB1>(R);
-                Dd += pair_dpp<0xB1>(Dd);
-            } else {
-#pragma unroll
-                for (int off = 1; off < LPI; off <<= 1) {
-                    R += __shfl_xor(R, off, 64);
-                    Dd += __shfl_xor(Dd, off, 64);
-                }
+            R += pair_dpp<0xB1>(R);
+            Dd += pair_dpp<0xB1>(Dd);
+            if (LPI == 4) {
+                R += pair_dpp<0x4E>(R);
+                Dd += pair_dpp<0x4E>(Dd);
             }
             const double lam = (double)A_[MP * MP + p] + bet * R;
             // 1 / lambda: hardware reciprocal and two Newton steps
@@ -782,14 +791,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             if (c == j % LPI) {
                 lo[j / LPI] = lam;
                 ro[j / LPI] = w * (R - bet * Dd);
-                atomicAdd(&sce[p], w);
-                atomicAdd(&sce[MP + p], 1.0 - ex);
-                atomicAdd(&sce[2 * MP + p], (T - te) * ex);
+                if (LPI == 2) atomicAdd(&sce[2 * MP + p], (T - te) * ex);
             }
+            // the sums of the event's node, one to a lane: one LDS add for them
+            {
+                const double v = c == 0 ? w : c == 1 ? 1.0 - ex : (T - te) * ex;
+                if (LPI == 2 || c < 3) atomicAdd(&sce[c * MP + p], v);
+            }
+            if constexpr (GL) {
 #pragma unroll
-            for (int u = 0; u < CL; ++u)
+                for (int u = 0; u < CL; ++u) atomicAdd(&gl[u * GR + p * LPI + c], w * K[u]);
+            } else {
+                // w on the event's row; the others' factor keeps w's low word
+                // (at most a denormal: nothing beside a sum of weights), one
+                // select instead of two
 #pragma unroll
-                for (int r = 0; r < MP; ++r) Gc[r][u] = __builtin_fma(r == p ? w : 0.0, K[u], Gc[r][u]);
+                for (int r = 0; r < MP; ++r) {
+                    const double wr = __hiloint2double(r == p ? __double2hiint(w) : 0, __double2loint(w));
+#pragma unroll
+                    for (int u = 0; u < CL; ++u) Gc[r][u] = __builtin_fma(wr, K[u], Gc[r][u]);
+                }
+            }
             tp = te;
             mp = p;
         }
@@ -831,7 +853,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         o[4 + qa + u] = sce[qa + u];
         o[4 + MP + qa + u] = sce[MP + qa + u];
 #pragma unroll
-        for (int r = 0; r < MP; ++r) o[4 + 2 * MP + r * MP + qa + u] = Gc[r][u];
+        for (int r = 0; r < MP; ++r) o[4 + 2 * MP + r * MP + qa + u] = GL ? gl[u * GR + r * LPI + c] : Gc[GL ? 0 : r][u];
     }
 }
 
@@ -926,6 +948,14 @@ __global__ __launch_bounds__(1024) void small_reduce2(int32_t S, int64_t n_chunk
 }
 
 // ---------------------------------------------------------------- host launch
+// Gradient, MP >= 4: four lanes an item, its dL/dalpha block in LDS, up to
+// HK_GL_ITEMS MP items (more waves and a shorter chain per event: 48 sequences
+// of 100 to 2000 events 21 / 15 us with two / four lanes; 1e6 events, M = 3, 102
+// / 95 a call); beyond, two lanes with the block in registers (the chip is full;
+// bound by the vector ALU, busy 91% of the time, where four lanes do more in
+// all: 6.3e7 events in 4096 sequences 1004 / 1116 us; 3e6 events, M = 4, 161 /
+// 163 a call).
+#define HK_GL_ITEMS 4096
 template <int MP>
 static hawkes_status run_small_mp(const SmallArgs& A, hipStream_t st) {
     const int32_t PW = A.grad ? 4 + 2 * MP + MP * MP : 2;
@@ -946,11 +976,17 @@ static hawkes_status run_small_mp(const SmallArgs& A, hipStream_t st) {
     bool done = false;
     if constexpr (MP >= 4) {
         if (A.grad) {
-            constexpr int LPI = 2;   // lanes per item (4 measured slower for MP = 8)
-            const int64_t wc = (A.n_items_cap * LPI + 63) / 64;
-            hipLaunchKernelGGL((small_compute_c<MP, LPI>), dim3((unsigned)((wc + 3) / 4)), dim3(256), 0, st, A.S,
-                               A.n_total, A.ev_off, A.item_off, A.L, A.t, A.marks, A.m_s, A.T_s, A.mu, A.alpha,
-                               A.beta, A.mu_off, A.a_off, A.item_pref, A.tile_carry, A.part, PW, A.n_items_cap);
+            // lanes per item
+            auto launch = [&](auto* kern, int lpi) {
+                const int64_t wc = (A.n_items_cap * lpi + 63) / 64;
+                hipLaunchKernelGGL(kern, dim3((unsigned)((wc + 3) / 4)), dim3(256), 0, st, A.S, A.n_total, A.ev_off,
+                                   A.item_off, A.L, A.t, A.marks, A.m_s, A.T_s, A.mu, A.alpha, A.beta, A.mu_off,
+                                   A.a_off, A.item_pref, A.tile_carry, A.part, PW, A.n_items_cap);
+            };
+            if (A.n_items_cap <= HK_GL_ITEMS * MP)
+                launch(small_compute_c<MP, 4, true>, 4);
+            else
+                launch(small_compute_c<MP, 2, false>, 2);
             done = true;
         }
     }

@@ -1,9 +1,11 @@
 """The engine for up to 8 nodes at its edges, against the FP64 oracle (1e-6
 relative per output block).  One sequence: items in one wave, at 16 and 17
 waves (the scan over waves takes 16 at a time), below and above 2048 items
-(one or two levels of sums) and at the first longer item.  Batches: fewer and
+(one or two levels of sums), around 16384 items (four or two lanes an item) and
+at the first longer item.  Batches: fewer and
 more than 64 sequences (the threads of the last sums), 1024 and 1025 (the
-setup's rounds), with empty sequences among them."""
+setup's rounds), with empty sequences among them, and more
+than 32768 items (two lanes an item at 8 nodes)."""
 import types
 
 import numpy as np
@@ -17,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,n", [(1, 1), (2, 16), (8, 17), (3, 1024), (5, 1025), (1, 16384), (2, 16385), (4, 17409),
-                                 (8, 32735), (8, 32752), (1, 32768), (1, 393231), (2, 393232)])
+                                 (8, 32735), (8, 32752), (1, 32768), (1, 393231), (2, 393232), (3, 262111), (3, 262144)])
 def test_one_sequence(H, M, n):  # noqa: F811
     import torch
     t, m, mu, alpha, beta, T = rand_problem(900 + M + n, n, M, ties=True, density=0.7, rate=20.0)
@@ -28,7 +30,8 @@ def test_one_sequence(H, M, n):  # noqa: F811
     assert scalar_rel(ll.item(), ref[0]) < 1e-6
 
 
-@pytest.mark.parametrize("S,hi", [(63, 400), (64, 400), (65, 3000), (40, 5000), (1024, 30), (1025, 30), (2100, 20)])
+@pytest.mark.parametrize("S,hi", [(63, 400), (64, 400), (65, 3000), (40, 5000), (1024, 30), (1025, 30), (2100, 20),
+                                  (16, 120000)])
 def test_batch(H, S, hi):  # noqa: F811
     rng = np.random.default_rng(S)
     lens = rng.integers(1, hi, S)
