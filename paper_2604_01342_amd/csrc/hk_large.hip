@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void large_scan_local(int32_t nseg, int32_t M,
 #pragma unroll
         for (int v = 0; v < HK_SG; ++v)
             if (v < u) D += sp[v];
-        const double e = exp(-b0 * D);
+        const double e = exp_f64(-b0 * D);
         if (u < s1 - s0) {
             seg_off[s0 + u] = D;
             seg_offdec[s0 + u] = e;
@@ -250,26 +250,37 @@ __global__ __launch_bounds__(256) void large_scan_local(int32_t nseg, int32_t M,
     }
     double K = 0.0, J = 0.0;
     const double bq = beta_pt ? (double)beta_pt[q] : 0.0;
-    // the group's segment maps of node q, all loads issued up front
-    double rk[HK_SG], rj[HK_SG];
+    // the group's segment maps of node q, spans and decays, 16 segments at a
+    // time: their loads and exponentials before the chain (two multiply-adds
+    // a segment).  With the spans and decays read inside the chain it was 32
+    // dependent loads (us a launch, M = 251: 12, 6 now; M = 1000: 13, 8).
+    constexpr int PF = 16;
 #pragma unroll
-    for (int u = 0; u < HK_SG; ++u) {
-        const int32_t s = s0 + u < s1 ? s0 + u : s1 - 1;
-        rk[u] = agg[(int64_t)s * 2 * M + q];
-        rj[u] = agg[(int64_t)s * 2 * M + M + q];
-    }
+    for (int h = 0; h < HK_SG; h += PF) {
+        double rk[PF], rj[PF], D[PF], ex[PF];
 #pragma unroll
-    for (int u = 0; u < HK_SG; ++u) {
-        const int32_t s = s0 + u;
-        if (s < s1) {
-            double* o = carry_seg + (int64_t)s * 2 * M;
-            o[q] = K;
-            o[M + q] = J;
-            const double D = seg_span[s];
-            const double ex = beta_pt ? exp(-bq * D) : seg_dec[s];
-            const double k0 = K;
-            K = __builtin_fma(ex, k0, rk[u]);
-            J = __builtin_fma(ex, __builtin_fma(D, k0, J), rj[u]);
+        for (int u = 0; u < PF; ++u) {
+            const int32_t s = s0 + h + u < s1 ? s0 + h + u : s1 - 1;
+            rk[u] = agg[(int64_t)s * 2 * M + q];
+            rj[u] = agg[(int64_t)s * 2 * M + M + q];
+            D[u] = seg_span[s];
+            ex[u] = beta_pt ? 0.0 : seg_dec[s];
+        }
+        if (beta_pt) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bq * D[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int32_t s = s0 + h + u;
+            if (s < s1) {
+                double* o = carry_seg + (int64_t)s * 2 * M;
+                o[q] = K;
+                o[M + q] = J;
+                const double k0 = K;
+                K = __builtin_fma(ex[u], k0, rk[u]);
+                J = __builtin_fma(ex[u], __builtin_fma(D[u], k0, J), rj[u]);
+            }
         }
     }
     gagg[(int64_t)g * 2 * M + q] = K;
@@ -285,15 +296,21 @@ __global__ __launch_bounds__(256) void large_scan_groups(int32_t nseg, int32_t M
     const int32_t ngr = (nseg + HK_SG - 1) / HK_SG;
     double K = carry[q], J = carry[M + q];
     const double bq = beta_pt ? (double)beta_pt[q] : 0.0;
-    // 16 group maps of node q at a time, their loads issued up front
+    // 16 group maps of node q at a time, their loads and decays up front
     constexpr int PF = 16;
     for (int32_t g0 = 0; g0 < ngr; g0 += PF) {
-        double gk[PF], gj[PF];
+        double gk[PF], gj[PF], D[PF], ex[PF];
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int32_t g = g0 + u < ngr ? g0 + u : ngr - 1;
             gk[u] = gagg[(int64_t)g * 2 * M + q];
             gj[u] = gagg[(int64_t)g * 2 * M + M + q];
+            D[u] = gspan[g];
+            ex[u] = beta_pt ? 0.0 : gdec[g];
+        }
+        if (beta_pt) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bq * D[u]);
         }
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
@@ -301,11 +318,9 @@ __global__ __launch_bounds__(256) void large_scan_groups(int32_t nseg, int32_t M
             if (g < ngr) {
                 gcarry[(int64_t)g * 2 * M + q] = K;
                 gcarry[(int64_t)g * 2 * M + M + q] = J;
-                const double D = gspan[g];
-                const double ex = beta_pt ? exp(-bq * D) : gdec[g];
                 const double k0 = K;
-                K = __builtin_fma(ex, k0, gk[u]);
-                J = __builtin_fma(ex, __builtin_fma(D, k0, J), gj[u]);
+                K = __builtin_fma(ex[u], k0, gk[u]);
+                J = __builtin_fma(ex[u], __builtin_fma(D[u], k0, J), gj[u]);
             }
         }
     }

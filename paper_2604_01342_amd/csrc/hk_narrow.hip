@@ -155,6 +155,9 @@ __global__ __launch_bounds__(64 * NA_W) __attribute__((amdgpu_waves_per_eu(4))) 
         };
         ld(0);
         for (int bt = 0; bt < 4; ++bt) {
+            // pass 1 (a chain) before other waves' pass 2 (LDS adds): 92 / 88
+            // us at M = 50, 1e6 events
+            __builtin_amdgcn_s_setprio(2);
             const int64_t i = ga + bt * LG + l;
             const bool valid = i < b;
             if (__ballot(valid) == 0) break;
@@ -223,6 +226,7 @@ __global__ __launch_bounds__(64 * NA_W) __attribute__((amdgpu_waves_per_eu(4))) 
                 }
             }
             if (GRAD) {
+                __builtin_amdgcn_s_setprio(0);
                 // pass 2
                 if (LG < 64) {
                     stA[wv][lane] = make_double2(d, c);
