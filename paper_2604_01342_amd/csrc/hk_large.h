@@ -158,7 +158,7 @@ void large_index_launch(const LargeArgs& A, int trans, int32_t* ptr, int2* cv, i
 // and at least one spare entry past the M^2 a dense alpha fills
 inline int64_t cv_stride(int64_t MM) { return (MM + 2) & ~(int64_t)1; }
 // apply = false leaves carry_seg as in-group prefixes (the forward pass and
-// the checkpoint kernel then add the group carries themselves)
+// dense_prep then add the group carries themselves)
 void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st, bool apply = true);
 void large_chunk_acc_launch(int32_t nseg, int32_t width, const double* seg_part, double* acc, hipStream_t st);
 void bucket_chunk(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, const float* wchunk, int bs, hipStream_t st);

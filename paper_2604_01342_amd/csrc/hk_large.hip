@@ -1069,12 +1069,30 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         }
         A.ER = er < 1 ? 1 : (int32_t)er;
     } else if (A.per_target) {
-        // event ranges of the per-target dense kernel: as many workgroups as
-        // run at once (one a CU), and some events for every wave
-        const int64_t ev = A.n < A.CH ? A.n : A.CH;
-        int64_t er = 256 / ((int64_t)A.NB * A.NB);
-        if (er > ev / (HK_PT_WAVE_EV * 16)) er = ev / (HK_PT_WAVE_EV * 16);
-        A.ER = er < 1 ? 1 : (int32_t)er;
+        // Event ranges of the per-target dense kernel, one workgroup a CU at a
+        // time: the number whose rounds of 256 workgroups take least, a
+        // workgroup 18 ns for each of its source block's events and 20 us
+        // beside them (measured at M = 4096), a range its partials cleared,
+        // read, written and summed; with some events for every wave and about
+        // 256 MiB of partials at most.  (M = 1450, 144 pairs of blocks, 3e6
+        // events: 4.9 ms a call; as one range 56% of the CUs.)
+        const int64_t ev = A.n < A.CH ? A.n : A.CH, nbb = (int64_t)A.NB * A.NB;
+        int64_t most = ev / (HK_PT_WAVE_EV * 16);
+        const int64_t fit = ((int64_t)256 << 20) / ((int64_t)A.M * A.M * 8);
+        if (most > fit && fit >= 256 / nbb) most = fit;   // (one round's ranges always)
+        const int64_t few = 768 / nbb > 8 ? 768 / nbb : 8;   // up to three rounds, or eight ranges
+        if (most > few) most = few;
+        double best = 0.0;
+        A.ER = 1;
+        for (int64_t er = 1; er <= most; ++er) {
+            const double cost = (double)((nbb * er + 255) / 256) *
+                                    (0.018 * (double)ev / (double)(A.NB * er) + 20.0) +
+                                (double)er * 24.0 * (double)A.M * (double)A.M / 4.5e6;
+            if (er == 1 || cost < best) {
+                best = cost;
+                A.ER = (int32_t)er;
+            }
+        }
         A.BL = 6;
     } else {
         // dense dL/dalpha (hk_dense.hip).  Events per block: the pair terms
