@@ -1071,11 +1071,12 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     } else if (A.per_target) {
         // Event ranges of the per-target dense kernel, one workgroup a CU at a
         // time: the number whose rounds of 256 workgroups take least, a
-        // workgroup 18 ns for each of its source block's events and 20 us
-        // beside them (measured at M = 4096), a range its partials cleared,
-        // read, written and summed; with some events for every wave and about
-        // 256 MiB of partials at most.  (M = 1450, 144 pairs of blocks, 3e6
-        // events: 4.9 ms a call; as one range 56% of the CUs.)
+        // workgroup 18 ns for each of its source block's events (measured at
+        // M = 4096) and 22 us beside them, a range the traffic of its partials
+        // (both set by calls of 1 to 4 ranges, us: M = 2100, 2e5 events 915 /
+        // 840 / 828 / 869, 6e4 events 598 / 608 / 625 / 646; M = 1450, 2e5
+        // 741 / 760 / 678 / 711; M = 3000, 3e5 1507 / 1479 / 1485 / 1565);
+        // with some events for every wave and about 256 MiB of partials at most.
         const int64_t ev = A.n < A.CH ? A.n : A.CH, nbb = (int64_t)A.NB * A.NB;
         int64_t most = ev / (HK_PT_WAVE_EV * 16);
         const int64_t fit = ((int64_t)256 << 20) / ((int64_t)A.M * A.M * 8);
@@ -1086,8 +1087,8 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         A.ER = 1;
         for (int64_t er = 1; er <= most; ++er) {
             const double cost = (double)((nbb * er + 255) / 256) *
-                                    (0.018 * (double)ev / (double)(A.NB * er) + 20.0) +
-                                (double)er * 24.0 * (double)A.M * (double)A.M / 4.5e6;
+                                    (0.018 * (double)ev / (double)(A.NB * er) + 22.0) +
+                                (double)er * 12.0 * (double)A.M * (double)A.M / 4.5e6;
             if (er == 1 || cost < best) {
                 best = cost;
                 A.ER = (int32_t)er;
