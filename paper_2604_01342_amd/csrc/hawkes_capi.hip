@@ -284,19 +284,46 @@ hawkes_status hawkes_intensity(const hawkes_problem* p, const double* t, const i
 
 // Batches with more than 8 nodes in some sequence: the small-M engine's
 // workspace for the whole batch (at 8 nodes), then the large-M engine's for
-// one sequence of up to n_total events and max_m nodes (constant beyond one
-// chunk), 256-byte aligned after it.
+// any one sequence of up to n_total events and max_m nodes (constant beyond one
+// chunk), 256-byte aligned after it.  The layout grows with the events, and with
+// the nodes where its choices stay the same; a choice that changes on the way
+// to max_m (longer blocks, float32 rows, column blocks, fewer event ranges) can
+// make it smaller, so the largest layout is that of the last node count of some
+// stretch of equal choices.  Each choice moves one way only as the nodes grow:
+// a stretch's first node count is found by bisection.
 static size_t batched_large_bytes(int64_t n_total, int32_t max_m, bool grad) {
-    hawkes_problem p;
-    memset(&p, 0, sizeof(p));
-    p.n = n_total;
-    p.m = max_m;
-    p.k = 1;
-    p.beta_mode = HAWKES_BETA_SHARED;
-    p.T = 1.0;
-    LargeArgs A;
-    memset(&A, 0, sizeof(A));
-    return large_layout(A, &p, grad, nullptr, 0);
+    auto layout = [&](int32_t m, LargeArgs& A) {
+        hawkes_problem p;
+        memset(&p, 0, sizeof(p));
+        p.n = n_total;
+        p.m = m;
+        p.k = 1;
+        p.beta_mode = HAWKES_BETA_SHARED;
+        p.T = 1.0;
+        memset(&A, 0, sizeof(A));
+        return large_layout(A, &p, grad, nullptr, 0);
+    };
+    auto same = [](const LargeArgs& a, const LargeArgs& b) {
+        return a.narrow == b.narrow && a.BL == b.BL && a.row64 == b.row64 && a.NCB == b.NCB && a.ER == b.ER &&
+               a.NSP == b.NSP;
+    };
+    size_t need = 0;
+    for (int32_t m = max_m; m > 8;) {
+        LargeArgs top, A;
+        const size_t b = layout(m, top);
+        if (b > need) need = b;
+        int32_t lo = 8, hi = m;   // the stretch starts in (lo, hi]
+        while (hi - lo > 1) {
+            const int32_t mid = lo + (hi - lo) / 2;
+            layout(mid, A);
+            if (same(A, top))
+                hi = mid;
+            else
+                lo = mid;
+        }
+        m = lo;
+    }
+    return need;
 }
 
 size_t hawkes_batched_workspace_bytes(int32_t S, int64_t n_total, int32_t max_m, int with_grad) {
