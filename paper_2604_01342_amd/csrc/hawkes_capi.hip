@@ -34,14 +34,25 @@ size_t small_layout(SmallArgs& A, int32_t S, int64_t n_total, int32_t max_m, boo
     // events per item: at least 16; for long inputs grow it so the item count
     // (and so the workspace) stays bounded.  A longer item is a longer serial
     // walk, more items are a longer chain over the waves' maps (one sequence)
-    // and more partials to add.  Us a call with 16 / 32 / 64 / 128 events, one
-    // sequence: 1e6 events, M = 1: 184 / 119 / 102 / 125, M = 5: 232 / 151 /
-    // 119 / 138; 1e5, M = 8: 63 / 63 / 89 / 126; batches: 2.9e6 events in 200:
-    // 114 / 92 / 94 / 109; 5e6 in 500, M = 8, 32 / 64 / 128: 182 / 162 / 178;
-    // 2e7 in 2000, M = 3, 64 / 128 / 256: 357 / 335 / 356; 6.3e7 in 4096 with
-    // 256 / 512 / 1024: 1240 / 1198 / 1184.
+    // and more partials to add.  One sequence: the walk grows with n / items,
+    // the chain with the items, so the best count grows with sqrt(n).  Us a call
+    // with 16 / 32 / 64 / 128 events, 1e6 events, M = 1: 184 / 119 / 102 / 125,
+    // M = 5: 232 / 151 / 119 / 138; 1e5, M = 8: 63 / 63 / 89 / 126; log-likelihood
+    // with 128 / 256 / 512 events, 5e6 events, M = 1: 201 / 222 / 343, M = 8: 325
+    // / 455 / 792; 256 / 512 / 1024, 1e7, M = 1: 277 / 366 / 631, M = 8: 513 /
+    // 824 / 1520; 512 / 1024 / 2048, 3e7, M = 1: 483 / 702 / 1242, M = 8: 978 /
+    // 1651 / 3078 (their gradients, M = 8: 270 / 250 / 307; 399 / 414 / 564; 730 /
+    // 784 / 1093: several lanes an item, so fewer items do).
+    // Batches: 2.9e6 events in 200: 114 / 92 / 94 / 109; 5e6 in 500, M = 8, 32 /
+    // 64 / 128: 182 / 162 / 178; 2e7 in 2000, M = 3, 64 / 128 / 256: 357 / 335 /
+    // 356; 6.3e7 in 4096 with 256 / 512 / 1024: 1240 / 1198 / 1184.
     int64_t L = 16;
-    const int64_t target_items = single ? 24576 : 163840;
+    int64_t target_items = 163840;
+    if (single) {
+        target_items = (int64_t)((grad && A.MP >= 4 ? 14.0 : 18.0) * sqrt((double)n_total));
+        if (target_items < 24576) target_items = 24576;
+        if (target_items > 65536) target_items = 65536;
+    }
     while (L < 4096 && n_total / L > (single || L >= 64 ? target_items : 98304)) L <<= 1;
     if (n_total / L > target_items) L = (n_total + target_items - 1) / target_items;
     // a tuned item length replaces this one unless it makes more items than the
