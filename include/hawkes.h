@@ -41,7 +41,8 @@
  *    float64 state and float64 accumulators with float32 decay factors
  *    (each exponent is formed and range-reduced in float64); from 384 nodes on
  *    the state between blocks of events enters in float32, in float32 sums of
- *    at most 128 blocks.
+ *    at most 128 blocks, unless the chunk has more than 2^24 events or the
+ *    tuning below sets dense_cols to 64 or 128 or dense_rows to 16.
  *    Every sum over events (log-likelihood, gradients) is accumulated in
  *    float64 in a fixed order, so repeated calls return bitwise-identical
  *    results, with one exception: in the large-M engine, dL/dalpha sums its
@@ -117,7 +118,8 @@ typedef struct hawkes_problem {
  * inputs, as the Python package's autotuner does.
  *   dense_cols    shared-decay large-M engine: events (columns of the pair
  *                 matrix) per block of the dense dL/dalpha kernels: 64, 128
- *                 or 256
+ *                 or 256 (64 and 128 are doubled above 512 nodes); with 64 or
+ *                 128 the state between blocks is float64
  *   dense_ranges  the same kernels: event ranges per chunk, each with its own
  *                 partial sums: a power of two, 1..4096 (fewer if a chunk
  *                 has fewer segments)
@@ -125,8 +127,9 @@ typedef struct hawkes_problem {
  *                 value too small for the engine's bound on the item count
  *                 (and so on its workspace) is raised to the smallest that
  *                 fits
- *   dense_rows    16 or 32, accepted for callers that set it: the dense
- *                 dL/dalpha tiles have 16 rows whatever it is */
+ *   dense_rows    16: the state between blocks and its sums are float64
+ *                 whatever the node count; 32: as 0 (the dense dL/dalpha tiles
+ *                 have 16 rows whatever it is) */
 typedef struct hawkes_tuning {
     int32_t dense_cols;
     int32_t dense_ranges;

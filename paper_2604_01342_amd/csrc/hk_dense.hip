@@ -276,9 +276,9 @@ __device__ __forceinline__ int32_t xcd_item(int32_t total) {
 // columns: hence the permuted records).
 //
 // Product (waves 0 .. HK_TGW - 1): wave v the tiles of 16 x 16 columns of the
-// column groups v, v + HK_TGW, ..; 16 x 16 x 4 MFMAs, float32 (M from
-// HK_F32_MIN_M: the accumulators go to the tile every HK_FLUSH blocks; float32
-// sums over at most that many terms) or float64.  Lane l holds
+// column groups v, v + HK_TGW, ..; 16 x 16 x 4 MFMAs, float32 (the accumulators
+// go to the tile every HK_FLUSH blocks; float32 sums over at most that many
+// terms) or float64 (the layout's row64).  Lane l holds
 // U[k + l / 16][row l mod 16], K[k + l / 16][column l mod 16]; result register
 // r is row 4 (l / 16) + r (float32) or 4 r + l / 16 (float64), column l mod 16.
 //
@@ -431,6 +431,7 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
                                                           const RT* __restrict__ urow, const RT* __restrict__ krow,
                                                           double* __restrict__ gpart, double* __restrict__ spart,
                                                           double* __restrict__ cpart, int first) {
+    static_assert(HK_CW64 <= 32 * HK_TGW * 3, "float64 rows: at most three column groups a wave");
     constexpr int NG = 1 << (BL - 6);   // groups of 64 records per block
     constexpr int NPW = HK_TW - HK_TGW;
     extern __shared__ double lds[];
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
                 product(std::integral_constant<int, 1>{});
             } else if (nm == 2) {
                 product(std::integral_constant<int, 2>{});
-            } else if (nm == 3 || sizeof(RT) == 8) {
+            } else if (nm == 3 || sizeof(RT) == 8) {   // (float64: HK_CW64 columns at most)
                 product(std::integral_constant<int, 3>{});
             } else {
                 product(std::integral_constant<int, 4>{});

@@ -9,6 +9,7 @@
 #endif
 #define HK_NARROW_MAX_M 64   // nodes up to which one kernel takes the forward pass and the gradient
 #define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32
+#define HK_CW64 384        // widest column block with U and K in float64
 #define HK_WIDE 60.0       // anchored-exponent limit inside one block of the dense gradient
 
 namespace hk {

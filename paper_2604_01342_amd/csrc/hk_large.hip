@@ -1103,10 +1103,22 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         // n = 3e5: 54 / 49 / 58; M = 700, 2^20: - / 223 / 203; M = 1000,
         // 2^20: - / 335 / 215 (an earlier form)
         A.BL = A.M > 512 ? 8 : A.M > 128 ? 7 : 6;
-        if (tu.dense_cols > 0) A.BL = tu.dense_cols == 256 ? 8 : tu.dense_cols == 128 ? 7 : 6;
-        // tiles of 16 rows x up to 1024 columns (128 KiB of LDS): one column
-        // block, or several of a multiple of 64 columns
-        A.NCB = (A.M + 1023) / 1024;
+        // (a set length, doubled above 512 nodes where it is shorter than the
+        // rule's: with float64 rows and 64 / 128 / 256 events, M = 1000, n =
+        // 1e6: 1695 / 859 / 605 us a call)
+        if (tu.dense_cols > 0) {
+            A.BL = tu.dense_cols == 256 ? 8 : tu.dense_cols == 128 ? 7 : 6;
+            if (A.M > 512 && A.BL < 8) ++A.BL;
+        }
+        // rows of U and K, and their product, in float32 from HK_F32_MIN_M nodes
+        // on; in float64 on chunks above 2^24 events and where a caller sets
+        // dense_cols to 64 or 128 or dense_rows to 16
+        A.row64 = A.M < HK_F32_MIN_M || lg > 24 || tu.dense_cols == 64 || tu.dense_cols == 128 || tu.dense_rows == 16;
+        // tiles of 16 rows x up to 1024 columns (128 KiB of LDS; 384 with
+        // float64 rows, whose product holds twice the registers a column): one
+        // column block, or several of a multiple of 64 columns
+        const int32_t widest = A.row64 ? HK_CW64 : 1024;
+        A.NCB = (A.M + widest - 1) / widest;
         A.CW = A.NCB == 1 ? (A.M + 15) & ~15 : (((A.M + A.NCB - 1) / A.NCB) + 63) & ~63;
         A.DRB = 4;
         A.NBO = (A.M + 15) >> 4;
@@ -1124,11 +1136,12 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         }
         A.ER = er < 1 ? 1 : (int32_t)er;
     }
-    // rows of the sums per node: one a range; of one size for up to 16 ranges
-    // where they are small beside the dL/dalpha partials
-    A.NSP = A.ER < 16 && !A.per_target && !A.narrow && A.K == 1 && A.NCB == 1 ? 16 : A.ER;
+    // rows of the sums per node: one a range; room for 16 where they are small
+    // beside the dL/dalpha partials (one kernel, one column block or float64
+    // rows), so that there the workspace of up to 16 ranges differs by the
+    // dL/dalpha partials alone
+    A.NSP = A.ER < 16 && !A.per_target && !A.narrow && A.K == 1 && (A.NCB == 1 || A.row64) ? 16 : A.ER;
     A.Mp = (A.M + 63) & ~63;
-    A.row64 = A.M < HK_F32_MIN_M;
     A.grad = grad;
     const int64_t M = A.M, MM = M * M, K = A.K;
     Carve c(ws, ws_bytes);
