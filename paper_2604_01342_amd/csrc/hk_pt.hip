@@ -1217,20 +1217,24 @@ __global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, i
             const double tk = __shfl(S.ct, kj & 63, 64);
             const double bo = (double)BL[pi];
             const double fo = own ? bo * wi * exp_f64(-bo * (O.ct - (kj < ns ? tk : tl))) : 0.0;
-            // the own event's target rides in the low mantissa bits of its
-            // weight (a change of at most 2^-45 relative), so one pair of
-            // readlanes gives both
-            const double fop = __longlong_as_double((__double_as_longlong(fo) & ~(long long)(B - 1)) | (long long)pi);
+            // the own event's lane rides in the 6 low mantissa bits of its
+            // weight (a change of at most 2^-46 relative), so one pair of
+            // readlanes gives both; which of the lane's two targets it is
+            // comes from a mask of the own list (scalar instructions)
+            const double fop = __longlong_as_double((__double_as_longlong(fo) & ~63ll) | (long long)(pi & 63));
+            const uint64_t upper = __ballot(pi >= 64);
+            static_assert(R == 2, "one bit for the target within a lane");
             int j = 0;
             // own events up to dk join A
             auto join = [&](int dk) {
                 for (; j < dk; ++j) {
                     const double f = rl_d(fop, j);
-                    const int q = (int)(__double_as_longlong(f) & (B - 1));
+                    const int q = (int)(__double_as_longlong(f) & 63);
+                    const int up = (int)((upper >> j) & 1);
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        if (R > 1 && (q >> 6) != r) continue;
-                        if (lane == (q & 63)) {
+                        if (up != r) continue;
+                        if (lane == q) {
                             Ab[r] += f;
                             // keeps the add under the lane's exec mask (else the
                             // compiler adds on every lane and selects: two more
