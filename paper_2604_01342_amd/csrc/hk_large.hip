@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void large_scan_local(int32_t nseg, int32_t M,
 #pragma unroll
         for (int v = 0; v < HK_SG; ++v)
             if (v < u) D += sp[v];
-        const double e = exp_f64(-b0 * D);
+        const double e = exp(-b0 * D);
         if (u < s1 - s0) {
             seg_off[s0 + u] = D;
             seg_offdec[s0 + u] = e;
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void large_scan_local(int32_t nseg, int32_t M,
         }
         if (beta_pt) {
 #pragma unroll
-            for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bq * D[u]);
+            for (int u = 0; u < PF; ++u) ex[u] = exp(-bq * D[u]);
         }
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void large_scan_groups(int32_t nseg, int32_t M
         }
         if (beta_pt) {
 #pragma unroll
-            for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bq * D[u]);
+            for (int u = 0; u < PF; ++u) ex[u] = exp(-bq * D[u]);
         }
 #pragma unroll
         for (int u = 0; u < PF; ++u) {

@@ -907,7 +907,7 @@ __global__ __launch_bounds__(256) void pt_rscan_local(int64_t c0, int64_t c1, in
 #pragma unroll
     for (int u = 0; u < HK_SG; ++u) ag[u] = aggA[(int64_t)(s0 + u < s1 ? s0 + u : s1 - 1) * M + p];
 #pragma unroll
-    for (int u = 0; u < HK_SG; ++u) ex[u] = exp_f64(-bp * (ts[u + 1] - ts[u]));
+    for (int u = 0; u < HK_SG; ++u) ex[u] = exp(-bp * (ts[u + 1] - ts[u]));
     double A = 0.0;
 #pragma unroll
     for (int u = HK_SG - 1; u >= 0; --u) {
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(256) void pt_rscan_groups(int64_t c0, int64_t c1, i
 #pragma unroll
         for (int u = 0; u < PF; ++u) ag[u] = rgagg[(int64_t)(gb - 1 - u > 0 ? gb - 1 - u : 0) * M + p];
 #pragma unroll
-        for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bp * (ts[u] - ts[u + 1]));
+        for (int u = 0; u < PF; ++u) ex[u] = exp(-bp * (ts[u] - ts[u + 1]));
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int32_t g = gb - 1 - u;
@@ -963,7 +963,7 @@ __global__ void pt_rscan_apply(int64_t c0, int64_t c1, int64_t n, double T, int3
     const int32_t s1 = (g + 1) * HK_SG < nseg ? (g + 1) * HK_SG : nseg;
     const double te = seg_first_time(t, c0, c1, n, seg, nseg, s1, T);
     const double ts = seg_first_time(t, c0, c1, n, seg, nseg, s, T);
-    rcarry_seg[(int64_t)s * M + p] += exp_f64(-(double)beta[p] * (te - ts)) * rgcarry[(int64_t)g * M + p];
+    rcarry_seg[(int64_t)s * M + p] += exp(-(double)beta[p] * (te - ts)) * rgcarry[(int64_t)g * M + p];
 }
 
 // First record of [lo, hi) (positions in the records of one node block, at most

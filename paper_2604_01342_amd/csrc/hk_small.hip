@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256) void small_tile_scan(int32_t S, int64_t n_item
             Jb[u] = tile_agg[tt * W + 2 + MP + q];
         }
 #pragma unroll
-        for (int u = 0; u < PF; ++u) ex[u] = exp_f64(-bet * D[u]);
+        for (int u = 0; u < PF; ++u) ex[u] = exp(-bet * D[u]);
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int64_t tt = tb + u;
