@@ -116,13 +116,15 @@ typedef struct hawkes_problem {
  * it is too small).  Set it between calls, not while calls run on other
  * threads.  Intended for callers that time candidate values on their own
  * inputs, as the Python package's autotuner does.
- *   dense_cols    shared-decay large-M engine: events (columns of the pair
- *                 matrix) per block of the dense dL/dalpha kernels: 64, 128
- *                 or 256 (64 and 128 are doubled above 512 nodes); with 64 or
- *                 128 the state between blocks is float64
+ *   dense_cols    shared-decay large-M engine (more than 64 nodes, or several
+ *                 decay kernels): events (columns of the pair matrix) per
+ *                 block of the dense dL/dalpha kernels: 64, 128 or 256 (64 and
+ *                 128 are doubled above 512 nodes); with 64 or 128 the state
+ *                 between blocks is float64
  *   dense_ranges  the same kernels: event ranges per chunk, each with its own
  *                 partial sums: a power of two, 1..4096 (fewer if a chunk
- *                 has fewer segments)
+ *                 has fewer segments).  Neither knob applies to one shared
+ *                 decay and up to 64 nodes, which one kernel takes
  *   item_log2     small-M engine: log2 of the events per lane item, 4..16; a
  *                 value too small for the engine's bound on the item count
  *                 (and so on its workspace) is raised to the smallest that

@@ -9,12 +9,14 @@ candidate is at least 1% faster), applies it with
 class, so that later processes skip the timing.
 
 Knobs (see include/hawkes.h):
-  dense_cols, dense_ranges   the shared-decay large-M engine (M > 8): events per
-                             block and event ranges of the dense dL/dalpha
+  dense_cols, dense_ranges   the shared-decay large-M engine (M > 64, or several
+                             decay kernels): events per block and event ranges
+                             of the dense dL/dalpha
   item_log2                  the small-M engine (M <= 8, single or batched):
                              events per lane item
 
-The per-target engine has no knobs.  The cache file is
+The per-target engine and the one for 9 to 64 nodes and one shared decay have no
+knobs.  The cache file is
 $HAWKES_TUNE_CACHE, else ~/.cache/paper_2604_01342_amd/tuning.json.
 """
 from __future__ import annotations
@@ -52,19 +54,26 @@ def _bucket(x: int) -> int:
     return int(math.floor(math.log2(max(1, x))))
 
 
-def shape_class_single(n: int, M: int, per_target: bool, chunk_log2: int) -> str:
+def _narrow(M: int, per_target: bool, K: int) -> bool:
+    """Shapes that one kernel takes (9 to 64 nodes, one shared decay)."""
+    return not per_target and K == 1 and 8 < M <= 64
+
+
+def shape_class_single(n: int, M: int, per_target: bool, chunk_log2: int, K: int = 1) -> str:
     """Shapes that share a setting: M and n by powers of two, the decay mode,
-    the chunk size.  "blk": settings stored for the dense kernels before their
-    event blocks (tile widths) are not taken up."""
-    return f"single|M{_bucket(M)}|n{_bucket(n)}|pt{int(per_target)}|ch{chunk_log2 or 20}|blk"
+    the chunk size.  The shapes of one kernel have classes of their own; so have
+    those of the dense kernels' event blocks ("blk2"): settings stored for
+    earlier forms of these kernels are not taken up."""
+    kind = "|narrow" if _narrow(M, per_target, K) else "|blk2" if M > 8 and not per_target else ""
+    return f"single|M{_bucket(M)}|n{_bucket(n)}|pt{int(per_target)}|ch{chunk_log2 or 20}{kind}"
 
 
 def shape_class_batched(S: int, n_total: int, max_m: int) -> str:
     return f"batched|S{_bucket(S)}|n{_bucket(n_total)}|M{_bucket(max_m)}"
 
 
-def candidates_single(n: int, M: int, per_target: bool, chunk_log2: int) -> list[dict]:
-    if per_target:
+def candidates_single(n: int, M: int, per_target: bool, chunk_log2: int, K: int = 1) -> list[dict]:
+    if per_target or _narrow(M, per_target, K):
         return [{}]
     if M <= 8:
         return [{"item_log2": k} for k in range(4, 11)]
@@ -172,13 +181,14 @@ def tune_single(t, m, mu, alpha, beta, T, chunk_log2: int = 0, reps: int = 3, us
     M = int(mu.numel())
     per_target = int(beta.numel()) == M and M > 1
     n = int(t.numel())
-    key = shape_class_single(n, M, per_target, chunk_log2)
+    K = int(alpha.numel()) // (M * M)
+    key = shape_class_single(n, M, per_target, chunk_log2, K)
 
     def run() -> tuple:
         L, gmu, ga, gb = loglik_grad(t, m, mu, alpha, beta, T, chunk_log2)
         return L.reshape(1), gmu, ga, gb
 
-    return _search(key, candidates_single(n, M, per_target, chunk_log2), run, reps, use_cache, log)
+    return _search(key, candidates_single(n, M, per_target, chunk_log2, K), run, reps, use_cache, log)
 
 
 def tune_batched(b: Batch, reps: int = 3, use_cache: bool = True,

@@ -1060,13 +1060,11 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     A.narrow = !A.per_target && A.K == 1 && A.M <= HK_NARROW_MAX_M;
     if (A.narrow) {
         // workgroups (each with its partial sums), two segments a round: two
-        // a CU where the sequence has that many
+        // a CU where the sequence has that many.  dense_ranges does not apply: it
+        // would bound the workgroups of the whole pass, log-likelihood and
+        // intensities included
         const int64_t segs = A.n < A.CH ? (A.n + HK_SEG - 1) / HK_SEG : A.nseg;
-        int64_t er = (segs + 1) / 2 < 512 ? (segs + 1) / 2 : 512;
-        if (tu.dense_ranges > 0) {
-            er = tu.dense_ranges;
-            while (er > A.nseg) er >>= 1;
-        }
+        const int64_t er = (segs + 1) / 2 < 512 ? (segs + 1) / 2 : 512;
         A.ER = er < 1 ? 1 : (int32_t)er;
     } else if (A.per_target) {
         // Event ranges of the per-target dense kernel, one workgroup a CU at a
