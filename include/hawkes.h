@@ -186,6 +186,8 @@ hawkes_status hawkes_loglik_grad(const hawkes_problem* p,
  * Limit: problems whose hawkes_workspace_bytes(p, 1) exceeds
  * HAWKES_NOALLOC_SCRATCH_BYTES return HAWKES_EWORKSPACE before anything is
  * launched; a smaller chunk_log2 shrinks the workspace of long sequences.
+ * (With one of the dense kernels' knobs set such a problem is still taken
+ * where longer blocks, fewer ranges or chunks half as long fit.)
  * Argument errors return what hawkes_loglik_grad returns.
  * Every call on a device shares that device's array, which keeps the last
  * call's contents (each call re-initialises what it needs): calls that may

@@ -206,7 +206,7 @@ static hawkes_status mask_support(const hawkes_problem* p, const float* alpha, d
 static hawkes_status run_single(const hawkes_problem* p, const double* t, const int32_t* marks, const float* mu,
                                 const float* alpha, const float* beta, double* loglik, double* g_mu,
                                 double* g_alpha, double* g_beta, float* lambda_out, bool grad, void* ws,
-                                size_t ws_bytes, hipStream_t stream, bool support = false) {
+                                size_t ws_bytes, hipStream_t stream, bool support = false, size_t fit = 0) {
     if (!problem_ok(p) || !mu || !alpha || !beta) return HAWKES_EINVAL;
     if (!loglik && !lambda_out) return HAWKES_EINVAL;
     if (p->n > 0 && (!t || !marks)) return HAWKES_EINVAL;
@@ -229,7 +229,7 @@ static hawkes_status run_single(const hawkes_problem* p, const double* t, const 
     }
     LargeArgs A;
     memset(&A, 0, sizeof(A));
-    const size_t need = large_layout(A, p, grad, ws, ws_bytes);
+    const size_t need = large_layout(A, p, grad, ws, ws_bytes, fit);
     if (ws_bytes < need) return HAWKES_EWORKSPACE;
     if (((uintptr_t)ws & 255) != 0) return HAWKES_EWORKSPACE;
     A.t = t; A.marks = marks; A.mu = mu; A.alpha = alpha; A.beta = beta;
@@ -263,17 +263,23 @@ hawkes_status hawkes_loglik_grad_noalloc(const hawkes_problem* p, const double* 
                                          double* g_mu, double* g_alpha, double* g_beta, hipStream_t stream) {
     // every host check of hawkes_loglik_grad first, so that a bad argument
     // gives the same status; then the problem's workspace must fit the
-    // fixed scratch
+    // fixed scratch (with the dense kernels tuned: some layout of it)
     if (!problem_ok(p) || !mu || !alpha || !beta || !loglik) return HAWKES_EINVAL;
     if (p->n > 0 && (!t || !marks)) return HAWKES_EINVAL;
-    const size_t need = hawkes_workspace_bytes(p, 1);
+    const size_t fit = (size_t)HAWKES_NOALLOC_SCRATCH_BYTES;
+    size_t need = hawkes_workspace_bytes(p, 1);
     if (need == 0) return HAWKES_EUNSUPPORTED;
-    if (need > (size_t)HAWKES_NOALLOC_SCRATCH_BYTES) return HAWKES_EWORKSPACE;
+    if (need > fit && !use_small(p)) {
+        LargeArgs A;
+        memset(&A, 0, sizeof(A));
+        need = large_layout(A, p, true, nullptr, 0, fit);
+    }
+    if (need > fit) return HAWKES_EWORKSPACE;
     void* ws = nullptr;
     const hawkes_status st = scratch_address(&ws);
     if (st != HAWKES_OK) return st;
-    return run_single(p, t, marks, mu, alpha, beta, loglik, g_mu, g_alpha, g_beta, nullptr, true, ws,
-                      (size_t)HAWKES_NOALLOC_SCRATCH_BYTES, stream);
+    return run_single(p, t, marks, mu, alpha, beta, loglik, g_mu, g_alpha, g_beta, nullptr, true, ws, fit, stream,
+                      false, fit);
 }
 
 hawkes_status hawkes_loglik_grad_support(const hawkes_problem* p, const double* t, const int32_t* marks,

@@ -142,7 +142,10 @@ struct FwdExtra {
 };
 #define HK_PTCK 64         // checkpoint slots per level of the per-target gradient (at most 64^2 chunks)
 
-size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, size_t ws_bytes);
+// the workspace of p, carved from ws if not null; its size.  fit: if not 0 and
+// the size is above it, a layout of at most that size where there is one (with
+// the dense kernels tuned: longer blocks, fewer ranges, chunks half as long)
+size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, size_t ws_bytes, size_t fit = 0);
 hawkes_status run_large(LargeArgs& A, hipStream_t st);
 hawkes_status run_large_pt(LargeArgs& A, hipStream_t st);
 // helpers shared by the two large-M paths (host side)

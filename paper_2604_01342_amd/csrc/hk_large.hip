@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(64) void large_sup_scatter(int32_t M, int32_t ncopy
 }
 
 // ------------------------------------------------------------------ host
-size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, size_t ws_bytes) {
+static void large_rules(LargeArgs& A, const hawkes_problem* p, const hawkes_tuning& tu) {
     A.n = p->n;
     A.M = p->m;
     A.K = p->k;
@@ -1053,7 +1053,6 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
             A.seg >>= 1;
     A.nseg = (int32_t)((A.CH + A.seg - 1) / A.seg);
     A.NB = (A.M + HK_PT_NB - 1) / HK_PT_NB;
-    const hawkes_tuning tu = tuning_snapshot();
     // few nodes, one kernel: hk_narrow.hip, up to the 64 lanes of a wave.  The
     // forward pass, partition and dense kernels against it, n = 1e6: M = 16:
     // 87 + 14 + 86 us against 44; M = 50, dense rows: 119 + 13 + 119 against 95
@@ -1140,6 +1139,10 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
     // dL/dalpha partials alone
     A.NSP = A.ER < 16 && !A.per_target && !A.narrow && A.K == 1 && (A.NCB == 1 || A.row64) ? 16 : A.ER;
     A.Mp = (A.M + 63) & ~63;
+}
+
+// carves the workspace of A's choices; its size (pointers with ws not null)
+static size_t large_carve(LargeArgs& A, bool grad, void* ws, size_t ws_bytes) {
     A.grad = grad;
     const int64_t M = A.M, MM = M * M, K = A.K;
     Carve c(ws, ws_bytes);
@@ -1217,6 +1220,43 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
         }
     }
     return c.off + 256;
+}
+
+size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, size_t ws_bytes, size_t fit) {
+    const hawkes_tuning tu = tuning_snapshot();
+    large_rules(A, p, tu);
+    const bool tuned = tu.dense_ranges > 0 || tu.dense_cols > 0 || tu.dense_rows > 0;
+    if (fit > 0 && grad && !A.narrow && !A.per_target &&
+        large_carve(A, true, nullptr, 0) > fit) {
+        // no spare rows of the sums per node; with the dense kernels tuned longer
+        // blocks, then fewer ranges, then (not far above) the same with chunks
+        // half as long
+        hawkes_problem h = *p;
+        LargeArgs B = A;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (;;) {
+                B.NSP = B.ER;
+                if (large_carve(B, true, nullptr, 0) <= fit) {
+                    A = B;
+                    return large_carve(A, true, ws, ws_bytes);
+                }
+                if (!tuned)
+                    break;
+                else if (B.BL < 8)
+                    ++B.BL;
+                else if (B.ER > 1)
+                    B.ER >>= 1;
+                else
+                    break;
+            }
+            h.chunk_log2 = 0;
+            while (((int64_t)2 << h.chunk_log2) < A.CH) ++h.chunk_log2;
+            if (!tuned || h.chunk_log2 < 12 || large_carve(B, true, nullptr, 0) > fit + fit / 2) break;
+            B = A;
+            large_rules(B, &h, tu);
+        }
+    }
+    return large_carve(A, grad, ws, ws_bytes);
 }
 
 void large_chunk_acc_launch(int32_t nseg, int32_t width, const double* seg_part, double* acc, hipStream_t st) {
