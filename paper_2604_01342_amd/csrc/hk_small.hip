@@ -879,7 +879,7 @@ __global__ __launch_bounds__(1024) void small_reduce1(int32_t S, int64_t n_items
     int64_t i1e = item_off[s + 1];
     i1e = i1e > n_items_cap ? n_items_cap : i1e;
     const int64_t i1 = i0 + HK_RCH < i1e ? i0 + HK_RCH : i1e;
-    const int ns = 1024 / PW, e = threadIdx.x % PW, sl = threadIdx.x / PW;
+    const int ns = (int)blockDim.x / PW, e = threadIdx.x % PW, sl = threadIdx.x / PW;
     double acc = 0.0;
     if (sl < ns) {
 #pragma unroll 4
@@ -888,8 +888,9 @@ __global__ __launch_bounds__(1024) void small_reduce1(int32_t S, int64_t n_items
     sh[threadIdx.x] = acc;
     __syncthreads();
     if ((int)threadIdx.x < PW) {
+        const int nk = i1 - i0 < ns ? (int)(i1 - i0) : ns;   // slices with an item
         double v = 0.0;
-        for (int k = 0; k < ns; ++k) v += sh[k * PW + threadIdx.x];
+        for (int k = 0; k < nk; ++k) v += sh[k * PW + threadIdx.x];
         cpart[c * PW + threadIdx.x] = v;
     }
 }
@@ -922,8 +923,9 @@ __global__ __launch_bounds__(1024) void small_reduce2(int32_t S, int64_t n_chunk
     sh[threadIdx.x] = acc;
     __syncthreads();
     if ((int)threadIdx.x < PW) {
+        const int nk = c1 - c0 < ns ? (int)(c1 - c0) : ns;   // slices with a partial
         double v = 0.0;
-        for (int k = 0; k < ns; ++k) v += sh[k * PW + threadIdx.x];
+        for (int k = 0; k < nk; ++k) v += sh[k * PW + threadIdx.x];
         tot[threadIdx.x] = v;
     }
     __syncthreads();
@@ -1011,11 +1013,17 @@ static hawkes_status run_small_mp(const SmallArgs& A, hipStream_t st) {
     // up to 2048 items in all: one reduction of the items' partials (48
     // sequences of 100 to 2000 events: 12 us for the two levels, 4.6 for one)
     const bool one = A.n_items_cap <= 2048;
+    // level 1: a quarter of the threads where a chunk holds few items (2500
+    // sequences of one item, M = 1: 44 us a call, 54 with 1024 threads)
     if (!one)
-        hipLaunchKernelGGL(small_reduce1, dim3((unsigned)A.n_chunks_cap), dim3(1024), 0, st, A.S, A.n_items_cap,
+        hipLaunchKernelGGL(small_reduce1, dim3((unsigned)A.n_chunks_cap),
+                           dim3(A.n_items_cap < 8 * A.n_chunks_cap ? 256 : 1024), 0, st, A.S, A.n_items_cap,
                            A.item_off, A.chunk_off, A.part, PW, A.cpart, A.n_chunks_cap);
-    // few sequences: enough threads for their many chunks or items
-    const dim3 bd(A.S < 64 && (one || A.n_chunks_cap > 16) ? 1024 : 128);
+    // the last level: threads for the items of one long sequence, whatever the
+    // others (63 sequences of 16 events and one of 30,592, M = 8, 128 / 512 /
+    // 1024 threads: 173 / 66 / 57 us a call; 800 of 16, M = 1: 31 / 31 / 33), or
+    // for a few sequences' many chunks
+    const dim3 bd(one ? (A.S <= 512 ? 1024 : 512) : A.S < 64 && A.n_chunks_cap > 16 ? 1024 : 128);
     auto last = [&](auto* kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)A.S), bd, 0, st, A.S, one ? A.n_items_cap : A.n_chunks_cap,
                            one ? A.item_off : A.chunk_off, A.m_s, A.T_s, A.mu, A.beta, A.mu_off, A.a_off,
