@@ -1019,7 +1019,8 @@ __global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, i
                                                    const int32_t* __restrict__ bk_base,
                                                    const uint32_t* __restrict__ bk_key, const double* __restrict__ bk_t,
                                                    const float* __restrict__ bk_w, double* __restrict__ gpart,
-                                                   double* __restrict__ spart, double* __restrict__ npart) {
+                                                   double* __restrict__ spart, double* __restrict__ npart,
+                                                   int first) {
     constexpr int R = PT_DR, W = PT_DW, B = 64 * R, BS = 7, GS = B + 1;
     static_assert(B == 1 << BS && B == HK_PT_NB, "node blocks of the partition");
     extern __shared__ double lds[];
@@ -1068,23 +1069,27 @@ __global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, i
         bmax = o > bmax ? o : bmax;
     }
     double* gp = gpart + (int64_t)er * M * M;
-    // lanes over the block's columns (coalesced rows of gpart)
+    if (first) {
+        for (int x = threadIdx.x; x < B * GS; x += 64 * W) G[x] = 0.0;
+    } else {
+        // lanes over the block's columns (coalesced rows of gpart)
 #pragma unroll
-    for (int cg = 0; cg < R; ++cg) {
-        const int32_t col = s0 + 64 * cg + lane;
-        const int32_t cc = col < M ? col : M - 1;
-        for (int rg = wv * 8; rg < B; rg += 8 * W) {
-            double v[8];
+        for (int cg = 0; cg < R; ++cg) {
+            const int32_t col = s0 + 64 * cg + lane;
+            const int32_t cc = col < M ? col : M - 1;
+            for (int rg = wv * 8; rg < B; rg += 8 * W) {
+                double v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int32_t row = r0 + rg + j;
-                const int32_t rr = row < M ? row : M - 1;
-                v[j] = gp[(int64_t)rr * M + cc];
-            }
+                for (int j = 0; j < 8; ++j) {
+                    const int32_t row = r0 + rg + j;
+                    const int32_t rr = row < M ? row : M - 1;
+                    v[j] = gp[(int64_t)rr * M + cc];
+                }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int32_t row = r0 + rg + j;
-                G[(64 * cg + lane) * GS + rg + j] = (row < M && col < M) ? v[j] : 0.0;
+                for (int j = 0; j < 8; ++j) {
+                    const int32_t row = r0 + rg + j;
+                    G[(64 * cg + lane) * GS + rg + j] = (row < M && col < M) ? v[j] : 0.0;
+                }
             }
         }
     }
@@ -1295,9 +1300,13 @@ __global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, i
         if (sb == 0 && r0 + x < M) {
             double v = 0.0;
             for (int w = 0; w < W; ++w) v += G[B * GS + w * B + x];
-            spart[(int64_t)er * M + r0 + x] += v;
+            double* o = spart + (int64_t)er * M + r0 + x;
+            *o = first ? v : *o + v;
         }
-        if (rb == 0 && s0 + x < M) npart[(int64_t)er * M + s0 + x] += (double)NL[x];
+        if (rb == 0 && s0 + x < M) {
+            double* o = npart + (int64_t)er * M + s0 + x;
+            *o = first ? (double)NL[x] : *o + (double)NL[x];
+        }
     }
 }
 
@@ -1330,7 +1339,7 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
     Z.add(A.carry, 2 * (int64_t)M);
     Z.add(A.acc, 4);
     Z.add(A.ebacc, M);
-    if (A.grad) {
+    if (A.grad && A.nchunks == 0) {   // (the first chunk taken stores the partials)
         Z.add(A.gpart, (int64_t)A.ER * MM);
         Z.add(A.spart, (int64_t)A.ER * M);
         Z.add(A.cpart_, (int64_t)A.ER * M);
@@ -1472,7 +1481,8 @@ hawkes_status run_large_pt(LargeArgs& A, hipStream_t st) {
                 TimedScope ts(0, st);
                 hipLaunchKernelGGL(pt_dense, dim3(nblk), dim3(64 * PT_DW), PT_DENSE_LDS, st, c0, c1, A.n, A.T, M, A.NB,
                                    A.ER, A.seg, nseg, nsegb, A.t, A.beta, A.rcarry_seg, A.rgcarry, A.bk_off,
-                                   A.bk_base, A.bk_key, A.bk_t, A.bk_w, A.gpart, A.spart, A.cpart_);
+                                   A.bk_base, A.bk_key, A.bk_t, A.bk_w, A.gpart, A.spart, A.cpart_,
+                                   ch == A.nchunks - 1 ? 1 : 0);
             }
         }
     }
