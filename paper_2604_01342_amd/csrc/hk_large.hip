@@ -864,12 +864,17 @@ __global__ __launch_bounds__(256) void large_combine(int64_t c0, int64_t c1, int
 // ebacc: per-target decays, dL/dbeta = -ebacc, else null.
 // Every entry is summed over ER partials of dL/dalpha, and its column over NSC
 // partials of the weights and compensator terms, each in a fixed order: a
-// workgroup takes 16 columns and FR rows, its 16 thread rows are ES
-// slices of the partials times 16 / ES matrix rows, slice sums are added by a
+// workgroup takes CB columns and FR rows, its SR = 256 / CB thread rows are ES
+// slices of the partials times SR / ES matrix rows, slice sums are added by a
 // tree.  Bound by the read of the partials; with one thread per entry the 512
 // partials of a 16-node model were a chain of dependent loads (n = 1e6:
 // 123 us, and 35 us more for the column sums, against 10 us now).
-__device__ __forceinline__ double fin_tree(double v, double (*sh)[17], int c, int s, int w) {
+// CB = 16; 64 for many nodes with few partials (ES = 1): rows of alpha then start
+// anywhere in a cache line, and strips of 16 columns write two halves of lines
+// each (M = 6700, one range: 180 us with 64 columns, 228 with 16; M = 6000: 113,
+// in tiles of 16 x 16 entries 216).
+template <int SR, int CB>
+__device__ __forceinline__ double fin_tree(double v, double (*sh)[CB + 1], int c, int s, int w) {
     // sum of v over the w slices of this thread's group (w a power of two,
     // groups of w consecutive s), returned to the group's first slice
     sh[s][c] = v;
@@ -883,6 +888,7 @@ __device__ __forceinline__ double fin_tree(double v, double (*sh)[17], int c, in
     return r;
 }
 
+template <int CB>
 __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_t NSC, int32_t ES, double T,
                                                    const float* __restrict__ mu, const double* __restrict__ seg_part,
                                                    int32_t nslot, const double* __restrict__ acc,
@@ -892,10 +898,11 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
                                                    double* __restrict__ g_mu, double* __restrict__ g_alpha,
                                                    double* __restrict__ g_beta, double* __restrict__ csum, int grad,
                                                    int32_t K, int32_t NSP, int32_t FR) {
-    __shared__ double sh[16][17];
+    constexpr int SR = 256 / CB;
+    __shared__ double sh[SR][CB + 1];
     __shared__ double ps[256];
     const int64_t MM = (int64_t)M * M;
-    const int c = threadIdx.x & 15, s = threadIdx.x >> 4;
+    const int c = threadIdx.x & (CB - 1), s = threadIdx.x / CB;
     const int32_t k = blockIdx.z;
     if (gpart) gpart += (int64_t)k * ER * MM;
     if (grad) {
@@ -946,14 +953,14 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
         }
     }
     if (!grad) return;
-    const int32_t q = blockIdx.x * 16 + c;
+    const int32_t q = blockIdx.x * CB + c;
     const int32_t qc = q < M ? q : M - 1;
     // the columns' compensator sums (every workgroup of the columns), dL/dmu
     // and the per-target dL/dbeta (the first)
     double cs = 0.0;
 #pragma unroll 8
-    for (int32_t e = s; e < NSC; e += 16) cs += cpart[(int64_t)e * M + qc];
-    cs = fin_tree(cs, sh, c, s, 16);
+    for (int32_t e = s; e < NSC; e += SR) cs += cpart[(int64_t)e * M + qc];
+    cs = fin_tree<SR, CB>(cs, sh, c, s, SR);
     if (s == 0) ps[c] = cs;
     __syncthreads();
     cs = ps[c];
@@ -961,8 +968,8 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
         if (k == 0) {
             double v = 0.0;
 #pragma unroll 8
-            for (int32_t e = s; e < NSC; e += 16) v += spart[(int64_t)e * M + qc];
-            v = fin_tree(v, sh, c, s, 16);
+            for (int32_t e = s; e < NSC; e += SR) v += spart[(int64_t)e * M + qc];
+            v = fin_tree<SR, CB>(v, sh, c, s, SR);
             if (s == 0 && q < M && g_mu) g_mu[q] = v - T;
         }
         if (s == 0 && q < M) {
@@ -971,7 +978,23 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
         }
     }
     if (!g_alpha) return;
-    const int rw = 16 / ES, es = s & (ES - 1);
+    const int rw = SR / ES, es = s & (ES - 1);
+    if (ES == 1) {
+        // a thread an entry of each row: the rows' loads side by side
+#pragma unroll 4
+        for (int32_t r0 = 0; r0 < FR; r0 += SR) {
+            const int32_t row = blockIdx.y * FR + r0 + s;
+            if (row < M && q < M) {
+                const int64_t x = (int64_t)row * M + q;
+                double g = 0.0;
+                if (gpart)
+                    for (int32_t e = 0; e < ER; ++e) g += gpart[(int64_t)e * MM + x];
+                // gpart null: zero (large_sup_scatter then writes the support)
+                g_alpha[x] = gpart ? g - cs : 0.0;
+            }
+        }
+        return;
+    }
     for (int32_t r0 = 0; r0 < FR; r0 += rw) {
         const int32_t row = blockIdx.y * FR + r0 + s / ES;
         const int32_t rc = row < M ? row : M - 1;
@@ -981,8 +1004,7 @@ __global__ __launch_bounds__(256) void large_final(int32_t M, int32_t ER, int32_
 #pragma unroll 8
             for (int32_t e = es; e < ER; e += ES) g += gpart[(int64_t)e * MM + x];
         }
-        if (ES > 1) g = fin_tree(g, sh, c, s, ES);
-        // gpart null: zero (large_sup_scatter then writes the support)
+        g = fin_tree<SR, CB>(g, sh, c, s, ES);
         if (es == 0 && row < M && q < M) g_alpha[x] = gpart ? g - cs : 0.0;
     }
 }
@@ -994,16 +1016,25 @@ void large_final_launch(const LargeArgs& A, bool slots, const double* ebacc, con
     int32_t ES = 1;
     while (ES < 16 && A.ER > 8 * ES) ES <<= 1;
     // rows per workgroup: 16, or one pass of its thread rows where that leaves
-    // the chip idle (few nodes)
+    // the chip idle (few nodes); more with many nodes, so that a workgroup's
+    // column sums are made for more than a tile
     const int32_t M = A.M;
-    const unsigned gx = (unsigned)((M + 15) / 16);
-    const int32_t FR = (int64_t)gx * gx < 256 ? 16 / ES : 16;
+    const bool wide = ES == 1 && M >= 1024;
+    const unsigned gx = (unsigned)(wide ? (M + 63) / 64 : (M + 15) / 16);
+    int32_t FR = (int64_t)gx * gx < 256 && !wide ? 16 / ES : 16;
+    while ((int64_t)gx * (M / FR) > 8192) FR <<= 1;
     const unsigned gy = (unsigned)((M + FR - 1) / FR);
     const unsigned gz = (unsigned)A.K;
-    hipLaunchKernelGGL(large_final, A.grad ? dim3(gx, A.g_alpha ? gy : 1, gz) : dim3(1), dim3(256), 0, st, M, A.ER,
-                       A.ER, ES, A.T, A.mu, slots ? A.seg_part : (const double*)nullptr, A.nseg, A.acc, ebacc, gpart,
-                       A.spart, A.cpart_, A.loglik, A.g_mu, A.g_alpha, A.g_beta, csum, A.grad ? 1 : 0, A.K, A.NSP,
-                       FR);
+    auto go = [&](auto* kern) {
+        hipLaunchKernelGGL(kern, A.grad ? dim3(gx, A.g_alpha ? gy : 1, gz) : dim3(1), dim3(256), 0, st, M, A.ER,
+                           A.ER, ES, A.T, A.mu, slots ? A.seg_part : (const double*)nullptr, A.nseg, A.acc, ebacc,
+                           gpart, A.spart, A.cpart_, A.loglik, A.g_mu, A.g_alpha, A.g_beta, csum, A.grad ? 1 : 0,
+                           A.K, A.NSP, FR);
+    };
+    if (wide)
+        go(large_final<64>);
+    else
+        go(large_final<16>);
 }
 
 // support-restricted dL/dalpha: one wave per row p writes, for each nonzero
