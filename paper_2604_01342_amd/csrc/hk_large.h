@@ -156,7 +156,7 @@ hawkes_status dense_allow_lds(const LargeArgs& A);
 // colsums, index: whether column sums and nonzeros per row are wanted
 void large_setup_launch(const LargeArgs& A, int trans, bool colsums, bool index, const ZeroList& Z, hipStream_t st);
 void large_index_launch(const LargeArgs& A, int trans, int32_t* ptr, int2* cv, int4* node_info, float* csc_b,
-                        hipStream_t st);
+                        hipStream_t st, double* gsup = nullptr, int32_t ncopy = 0);
 // entries between consecutive kernels' packed rows of alpha: even (each
 // kernel's array starts 16-byte aligned for the forward pass's pair loads)
 // and at least one spare entry past the M^2 a dense alpha fills

@@ -45,7 +45,9 @@ namespace hk {
 //                 a wave a row), cleared arrays
 //   large_index   a wave a row: the row's start (the sum of the counts before
 //                 it), its nonzeros in column order, and its node record
-//                 (csr begin, csr end, mu, colsum): one 16-byte load per event
+//                 (csr begin, csr end, mu, colsum): one 16-byte load per event;
+//                 gsup (or null): the sums in the order of the nonzeros, cleared
+//                 in each of the ncopy copies
 // With trans the rows are the columns of alpha (compressed-column form).
 // blockIdx.y: the decay kernel.
 __device__ __forceinline__ float alpha_at(const float* __restrict__ alpha, int32_t M, int32_t r, int32_t c,
@@ -99,7 +101,8 @@ __global__ __launch_bounds__(1024) void large_index(int32_t M, const float* __re
                                                     const int32_t* __restrict__ rcnt, int32_t* __restrict__ ptr,
                                                     int2* __restrict__ cv, int64_t cvs, const float* __restrict__ mu,
                                                     const float* __restrict__ colsum, int4* __restrict__ node_info,
-                                                    const float* __restrict__ beta, float* __restrict__ csc_b) {
+                                                    const float* __restrict__ beta, float* __restrict__ csc_b,
+                                                    double* __restrict__ gsup, int32_t ncopy) {
     const int lane = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t k = blockIdx.y, p = blockIdx.x * 16 + r;
     if (p >= M) return;
@@ -127,6 +130,8 @@ __global__ __launch_bounds__(1024) void large_index(int32_t M, const float* __re
             const int32_t i = o + __builtin_popcountll(nz & (lane ? (~0ull >> (64 - lane)) : 0ull));
             cv[i] = make_int2(q, __float_as_int(a));
             if (csc_b) csc_b[i] = beta[q];
+            if (gsup)
+                for (int32_t c = 0; c < ncopy; ++c) gsup[(int64_t)c * M * M + i] = 0.0;
         }
         o += __builtin_popcountll(nz);
     }
@@ -142,10 +147,10 @@ void large_setup_launch(const LargeArgs& A, int trans, bool colsums, bool index,
 }
 
 void large_index_launch(const LargeArgs& A, int trans, int32_t* ptr, int2* cv, int4* node_info, float* csc_b,
-                        hipStream_t st) {
+                        hipStream_t st, double* gsup, int32_t ncopy) {
     hipLaunchKernelGGL(large_index, dim3((unsigned)((A.M + 15) / 16), (unsigned)A.K), dim3(1024), 0, st, A.M, A.alpha,
                        trans, A.rcnt, ptr, cv, cv_stride((int64_t)A.M * A.M), A.mu, A.colsum, node_info, A.beta,
-                       csc_b);
+                       csc_b, gsup, ncopy);
 }
 
 // ------------------------------------------------------------------ agg
@@ -1559,15 +1564,14 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
         }
     }
     A.carry_prefix = true;
-    // cleared: the carried state, the segment slots' sums over the chunks (one
-    // reduction after the last chunk) and the CSR-ordered sums
+    // cleared: the carried state and the segment slots' sums over the chunks
+    // (one reduction after the last chunk)
     ZeroList Z{};
     Z.add(A.carry, (int64_t)2 * M);
     Z.add(A.seg_part, (int64_t)A.nseg * 4);
     if (A.grad && A.nchunks == 0) dense_zero(A, Z);
-    if (sup) Z.add(A.gsup, ncopy * MM);
     large_setup_launch(A, 0, true, true, Z, st);
-    large_index_launch(A, 0, A.csr_ptr, A.csr_cv, A.node_info, nullptr, st);
+    large_index_launch(A, 0, A.csr_ptr, A.csr_cv, A.node_info, nullptr, st, sup ? A.gsup : nullptr, ncopy);
     for (int64_t ch = 0; ch < A.nchunks; ++ch) {
         const int64_t c0 = ch * A.CH;
         const int64_t c1 = c0 + A.CH < A.n ? c0 + A.CH : A.n;
