@@ -1538,8 +1538,9 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     if (A.grad && dense_allow_lds(A) != HAWKES_OK) return HAWKES_EUNSUPPORTED;
     const bool sup = A.grad && A.support;
     // support-restricted: the first term's copies (CSR order) take the place
-    // of the dense partials, up to 8 of them (a power of two)
-    const int32_t ncopy = A.ER >= 8 ? 8 : A.ER >= 4 ? 4 : A.ER >= 2 ? 2 : 1;
+    // of the dense partials, up to 32 of them (a power of two)
+    int32_t ncopy = 1;
+    while (ncopy < 32 && 2 * ncopy <= A.ER) ncopy <<= 1;
     if (sup) A.gsup = A.gpart;
     // the forward pass adds the scan's group carries itself (the scan's
     // apply pass is left out) and counts the partition (by blocks of 2^DRB
