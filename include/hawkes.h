@@ -118,9 +118,10 @@ typedef struct hawkes_problem {
  * inputs, as the Python package's autotuner does.
  *   dense_cols    shared-decay large-M engine (more than 64 nodes, or several
  *                 decay kernels): events (columns of the pair matrix) per
- *                 block of the dense dL/dalpha kernels: 64, 128 or 256 (64 and
- *                 128 are doubled above 512 nodes); with 64 or 128 the state
- *                 between blocks is float64
+ *                 block of the dense dL/dalpha kernels: 64, 128 or 256 (where
+ *                 the columns take several tiles: half the library's number,
+ *                 half of it, at least 512); with 64 or 128 the state between
+ *                 blocks is float64
  *   dense_ranges  the same kernels: event ranges per chunk, each with its own
  *                 partial sums: a power of two, 1..4096 (fewer if a chunk
  *                 has fewer segments).  Neither knob applies to one shared

@@ -10,6 +10,7 @@
 #define HK_NARROW_MAX_M 64   // nodes up to which one kernel takes the forward pass and the gradient
 #define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32
 #define HK_CW64 384        // widest column block with U and K in float64
+#define HK_LSLOTS(BL, NCB) ((1 << (BL)) + 64 * (NCB))   // record slots of a block of events
 #define HK_WIDE 60.0       // anchored-exponent limit inside one block of the dense gradient
 
 namespace hk {
@@ -30,7 +31,7 @@ struct LargeArgs {
     int32_t NB;           // per-target decays: node blocks of HK_PT_NB (partition and dense kernel)
     // shared decay: one kernel for few nodes (hk_narrow.hip), else hk_dense.hip
     bool narrow;
-    int32_t BL;           // log2 of the events per block (6, 7 or 8)
+    int32_t BL;           // log2 of the events per block (6, 7 or 8; 8, 9 or 10 with several column blocks)
     int32_t DRB;          // log2 of the rows per tile (4)
     int32_t CW, NCB;      // columns per tile (a multiple of 16), column blocks
     int32_t NSP;          // rows of spart and cpart_
@@ -70,7 +71,10 @@ struct LargeArgs {
     // dense gradient, shared decay: rows of U and K per block of events, pair
     // records per event (block order), and whether a block is wide
     double *urow, *krow;  // [CH >> BL][Mp] (and slack for a column block past the row); float32 unless row64
-    uint2* prec;          // [CH] place in the block << 16 | 8 mark (place 0xffff: none), e^{beta (t_j - tau_b)}
+    uint2* prec;          // [CH] place in the block << 16 | 8 column (place 0xffff: none), e^{beta (t_j - tau_b)};
+                          //   several column blocks: [CH >> BL][HK_LSLOTS], each column block's records of a
+                          //   block after another, in whole groups of 64
+    int32_t* plist;       // [CH >> BL][NCB + 1] first group of each column block's records (several of them)
     int32_t* wide;        // [CH >> BL]
     // per-target decays (R-form forward, reverse adjoint for the gradient)
     int32_t* csc_ptr;   // alpha by column: targets p of source q

@@ -1129,20 +1129,7 @@ static void large_rules(LargeArgs& A, const hawkes_problem* p, const hawkes_tuni
         }
         A.BL = 6;
     } else {
-        // dense dL/dalpha (hk_dense.hip).  Events per block: the pair terms
-        // cost half a block of records per event, the rank-one product M^2
-        // multiply-adds per block.  dense_prep + dense_tiles, us a launch with
-        // 64 / 128 / 256 events: M = 50, n = 1e6: 119 / 142 / 208; M = 251,
-        // n = 3e5: 54 / 49 / 58; M = 700, 2^20: - / 223 / 203; M = 1000,
-        // 2^20: - / 335 / 215 (an earlier form)
-        A.BL = A.M > 512 ? 8 : A.M > 128 ? 7 : 6;
-        // (a set length, doubled above 512 nodes where it is shorter than the
-        // rule's: with float64 rows and 64 / 128 / 256 events, M = 1000, n =
-        // 1e6: 1695 / 859 / 605 us a call)
-        if (tu.dense_cols > 0) {
-            A.BL = tu.dense_cols == 256 ? 8 : tu.dense_cols == 128 ? 7 : 6;
-            if (A.M > 512 && A.BL < 8) ++A.BL;
-        }
+        // dense dL/dalpha (hk_dense.hip)
         // rows of U and K, and their product, in float32 from HK_F32_MIN_M nodes
         // on; in float64 on chunks above 2^24 events and where a caller sets
         // dense_cols to 64 or 128 or dense_rows to 16
@@ -1152,7 +1139,28 @@ static void large_rules(LargeArgs& A, const hawkes_problem* p, const hawkes_tuni
         // column block, or several of a multiple of 64 columns
         const int32_t widest = A.row64 ? HK_CW64 : 1024;
         A.NCB = (A.M + widest - 1) / widest;
-        A.CW = A.NCB == 1 ? (A.M + 15) & ~15 : (((A.M + A.NCB - 1) / A.NCB) + 63) & ~63;
+        if (A.NCB == 1) {
+            // events per block: the pair terms cost half a block of records per
+            // event, the product M^2 multiply-adds per block.  dense_prep +
+            // dense_tiles, us a launch with 64 / 128 / 256 events: M = 50, n =
+            // 1e6: 119 / 142 / 208; M = 251, n = 3e5: 54 / 49 / 58; M = 700, 2^20:
+            // - / 223 / 203; M = 1000, 2^20: - / 335 / 215 (an earlier form)
+            A.BL = A.M > 512 ? 8 : A.M > 128 ? 7 : 6;
+            if (tu.dense_cols > 0) A.BL = tu.dense_cols == 256 ? 8 : tu.dense_cols == 128 ? 7 : 6;
+            A.CW = (A.M + 15) & ~15;
+        } else {
+            // several column blocks: an event meets half a block's records of
+            // each of them, so longer blocks (us a call with 256 / 512 / 1024
+            // events, n = 1e6: M = 1025: 625 / 541 / 743; 2048: 713 / 529 / 555;
+            // 2200: 1092 / 744 / 656; 4096: 2496 / 1487 / 1048; float64 rows, M =
+            // 512: 284 / 283 / 410; 1000: 636 / 499 / 627; 1500: 1023 / 724 / 643;
+            // 4096: 5094 / 2846 / 1895).  Tuned: for dense_cols = 64 and 128 half
+            // the rule's, for 256 at least 512.
+            A.BL = A.M > (A.row64 ? 1152 : 2048) ? 10 : A.M > 512 ? 9 : 8;
+            if (tu.dense_cols == 256 && A.BL < 9) A.BL = 9;
+            if ((tu.dense_cols == 64 || tu.dense_cols == 128) && A.BL > 8) --A.BL;
+            A.CW = (((A.M + A.NCB - 1) / A.NCB) + 63) & ~63;
+        }
         A.DRB = 4;
         A.NBO = (A.M + 15) >> 4;
         // event ranges: one round of workgroups (one a CU), and at least two
@@ -1245,7 +1253,8 @@ static size_t large_carve(LargeArgs& A, bool grad, void* ws, size_t ws_bytes) {
             const size_t rows = (size_t)(A.CH >> A.BL) * A.Mp + 1024;
             A.urow = c.take<double>(A.row64 ? rows : rows / 2);
             A.krow = c.take<double>(A.row64 ? rows : rows / 2);
-            A.prec = c.take<uint2>(A.CH);
+            A.prec = c.take<uint2>(A.NCB > 1 ? (size_t)(A.CH >> A.BL) * HK_LSLOTS(A.BL, A.NCB) : (size_t)A.CH);
+            if (A.NCB > 1) A.plist = c.take<int32_t>((size_t)(A.CH >> A.BL) * (A.NCB + 1));
             A.wide = c.take<int32_t>(A.CH >> A.BL);
             A.bo_cnt = c.take<int32_t>((size_t)A.NBO * A.nseg);
             A.bo_off = c.take<int32_t>((size_t)A.NBO * (A.nseg + 1));
@@ -1278,7 +1287,7 @@ size_t large_layout(LargeArgs& A, const hawkes_problem* p, bool grad, void* ws, 
                 }
                 if (!tuned)
                     break;
-                else if (B.BL < 8)
+                else if (B.BL < (B.NCB > 1 ? 10 : 8))
                     ++B.BL;
                 else if (B.ER > 1)
                     B.ER >>= 1;
