@@ -118,8 +118,8 @@ __global__ __launch_bounds__(64 * HK_PW) void dense_prep(int64_t c0, int32_t nev
                                                          int32_t* __restrict__ bbase, uint32_t* __restrict__ bo_key,
                                                          float2* __restrict__ bo_cw, double* __restrict__ bo_e,
                                                          uint2* __restrict__ prec, int32_t* __restrict__ wide,
-                                                         RT* __restrict__ urow, RT* __restrict__ krow, int32_t CW,
-                                                         int32_t NCB, int32_t cbits,
+                                                         RT* __restrict__ urow, RT* __restrict__ krow, int32_t rep,
+                                                         int32_t CW, int32_t NCB, int32_t cbits,
                                                          int32_t* __restrict__ plist) {
     constexpr int NBK = HK_SEG >> BL;            // blocks per segment
     constexpr int NBT = HK_SEG / 64 / HK_PW;     // batches per wave
@@ -277,8 +277,9 @@ __global__ __launch_bounds__(64 * HK_PW) void dense_prep(int64_t c0, int32_t nev
         lds_wait();   // the update before the next batch's reads
         if (ML || !krow) continue;
         // pair record, at its place by bank (past the events: last)
-        const int32_t pp = base + bank_place(v ? (mk & 15) : 16, lt);
-        prec[pp] = v ? make_uint2(((uint32_t)(i & ((1 << BL) - 1)) << 16) | (uint32_t)(8 * mk), (uint32_t)__float_as_int(bj[u]))
+        const int col = mk + M * (lane & (rep - 1));
+        const int32_t pp = base + bank_place(v ? (col & 15) : 16, lt);
+        prec[pp] = v ? make_uint2(((uint32_t)(i & ((1 << BL) - 1)) << 16) | (uint32_t)(8 * col), (uint32_t)__float_as_int(bj[u]))
                      : make_uint2(0xffff0000u, 0u);
     }
     if (!krow) return;
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
                                                           const int32_t* __restrict__ wide,
                                                           const RT* __restrict__ urow, const RT* __restrict__ krow,
                                                           double* __restrict__ gpart, double* __restrict__ spart,
-                                                          double* __restrict__ cpart, int first,
+                                                          double* __restrict__ cpart, int first, int32_t rep,
                                                           const int32_t* __restrict__ plist) {
     static_assert(HK_CW64 <= 32 * HK_TGW * 3, "float64 rows: at most three column groups a wave");
     // groups of 64 records per block; MC: of a list, held at a time
@@ -795,7 +796,9 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
         const int32_t row = rb * 16 + x / CW, colm = cb0 + x % CW;
         if (row < M && colm < M) {
             const int64_t o = (int64_t)row * M + colm;
-            gp[o] = first ? GP[x] : gp[o] + GP[x];
+            double v = GP[x];
+            for (int r = 1; r < rep; ++r) v += GP[x + r * M];   // the node's other columns
+            gp[o] = first ? v : gp[o] + v;
         }
     }
 }
@@ -853,7 +856,7 @@ void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipS
                                A.Mp, A.NBO, nbits, 4, A.T, A.t, A.marks, A.wchunk, A.beta, A.carry_seg,
                                A.carry_prefix ? A.gcarry : (const double*)nullptr, A.seg_offdec, nseg, A.bo_off,
                                A.bo_base, A.bo_key, A.bo_cw, A.bo_e, A.prec, A.wide, ur,
-                               sums_only ? (RT*)nullptr : kr, A.CW, A.NCB, cbits, A.plist);
+                               sums_only ? (RT*)nullptr : kr, A.rep, A.CW, A.NCB, cbits, A.plist);
         }
         TimedScope ts(0, st);
         auto tiles = [&](auto* kern, bool pairs, int32_t ncb) {
@@ -861,7 +864,7 @@ void large_dense_launch(LargeArgs& A, int64_t c0, int64_t c1, int32_t nseg, hipS
             hipLaunchKernelGGL(kern, dim3((unsigned)(((items + 7) / 8) * 8)), dim3(64 * HK_TW), tiles_lds(A, pairs),
                                st, c0, nev, A.M, A.Mp, A.CW, ncb, A.NBO, A.ER, nseg, A.t, A.beta, A.bo_off,
                                A.bo_base, A.bo_key, A.bo_cw, A.bo_e, A.prec, A.wide, ur, kr, A.gpart, A.spart,
-                               A.cpart_, first ? 1 : 0, A.plist);
+                               A.cpart_, first ? 1 : 0, A.rep, A.plist);
         };
         if (sums_only)
             tiles(dense_tiles<BL, RT, false, false>, false, 1);

@@ -34,6 +34,7 @@ struct LargeArgs {
     int32_t BL;           // log2 of the events per block (6, 7 or 8; 8, 9 or 10 with several column blocks)
     int32_t DRB;          // log2 of the rows per tile (4)
     int32_t CW, NCB;      // columns per tile (a multiple of 16), column blocks
+    int32_t rep;          // tile columns per node (a power of two; 1 but for few nodes)
     int32_t NSP;          // rows of spart and cpart_
     bool row64;           // rows of U and K in float64
     int32_t Mp;           // row length of urow and krow: M, padded to 64

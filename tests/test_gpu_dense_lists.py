@@ -2,7 +2,8 @@
 and column block), against the FP64 oracle (1e-6 relative per output block): the first node counts with two and three
 column blocks and with blocks of 512 and 1024 events, chunks that end inside a block and a group, several chunks;
 marks that all fall into one column block (a list of 16 groups) and into one row block (more own events of a block
-than one batch of 64, with such lists), blocks too long in time for anchored factors."""
+than one batch of 64, with such lists), blocks too long in time for anchored factors; and several columns a node
+below 33 nodes (several decay kernels)."""
 import numpy as np
 import pytest
 
@@ -28,3 +29,12 @@ def test_column_lists(H, M, n, chunk, rate, marks):  # noqa: F811
         m = np.where(m % 4 > 0, m % 16 + 32, m).astype(np.int32)
     p = (t, m, mu, alpha, beta, T)
     check(run_gpu(H, *p, chunk), oracle.forward(*p), label=f"lists M={M} n={n} {marks}")
+
+
+@pytest.mark.parametrize("M,K,n", [(1, 2, 3_000), (2, 3, 3_000), (3, 2, 1_025), (16, 2, 3_000), (31, 2, 3_000),
+                                   (32, 2, 3_000), (33, 2, 3_000)])
+def test_columns_of_few_nodes(H, M, K, n):  # noqa: F811
+    t, m, mu, alpha, _, T = rand_problem(M + K, n, M, ties=True, rate=5.0)
+    a = np.stack([alpha * np.float32(0.5 / (k + 1)) for k in range(K)])
+    p = (t, m, mu, a, np.array([1.0, 0.2, 5.0][:K], np.float32), T)
+    check(run_gpu(H, *p), oracle.forward(*p), label=f"columns M={M} K={K}")
