@@ -243,19 +243,22 @@ def _loglik_grad(t, m, mu, alpha, beta, T, chunk_log2, support=False, packed=Fal
     nb = L.hawkes_workspace_bytes(ctypes.byref(p), 1)
     ws = _workspace(dev, nb)
     M = mu.numel()
-    out = torch.empty(1, dtype=torch.float64, device=dev)
     if packed:
         na = alpha.numel()
+        out = torch.empty((), dtype=torch.float64, device=dev)
         g = torch.empty(M + na + beta.numel(), dtype=torch.float64, device=dev)
-        gmu, ga, gb = g[:M], g[M:M + na], g[M + na:]
+        at = g.data_ptr()
+        gp = ctypes.c_void_p(at), ctypes.c_void_p(at + 8 * M), ctypes.c_void_p(at + 8 * (M + na))
     else:
+        out = torch.empty(1, dtype=torch.float64, device=dev)
         gmu = torch.empty(M, dtype=torch.float64, device=dev)
         ga = torch.empty(_gshape(mu, alpha), dtype=torch.float64, device=dev)
         gb = torch.empty(beta.numel(), dtype=torch.float64, device=dev)
+        gp = _ptr(gmu), _ptr(ga), _ptr(gb)
     name = "hawkes_loglik_grad_support" if support else "hawkes_loglik_grad"
     _check(name, getattr(L, name)(ctypes.byref(p), _ptr(t), _ptr(m), _ptr(mu), _ptr(alpha), _ptr(beta), _ptr(out),
-                                  _ptr(gmu), _ptr(ga), _ptr(gb), _ptr(ws), nb, _stream(dev)))
-    return (out[0], g) if packed else (out[0], gmu, ga, gb)
+                                  *gp, _ptr(ws), nb, _stream(dev)))
+    return (out, g) if packed else (out[0], gmu, ga, gb)
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20   # HAWKES_NOALLOC_SCRATCH_BYTES
@@ -570,12 +573,18 @@ class HawkesLogLik(torch.autograd.Function):
         # converted are scaled as one tensor first: four launches for three
         # float32 parameters instead of six.
         g, = ctx.saved_tensors
-        parts = g.split([s.numel() for s in ctx.shapes])
-        if any(d != g.dtype for d in ctx.dtypes):
-            scaled = (gL * g).split([s.numel() for s in ctx.shapes])
-        out = [(gL * x if d == g.dtype else scaled[i].to(d)).reshape(s)
-               for i, (x, s, d) in enumerate(zip(parts, ctx.shapes, ctx.dtypes))]
-        return (*out, None, None, None, None)
+        (smu, sa, sb), types = ctx.shapes, ctx.dtypes
+        sizes = [smu.numel(), sa.numel(), sb.numel()]
+        if g.dtype in types:
+            scaled = (gL * g).split(sizes) if len(set(types)) > 1 else (None,) * 3
+            gmu, ga, gb = (gL * x if d == g.dtype else y.to(d)
+                           for x, y, d in zip(g.split(sizes), scaled, types))
+        else:
+            gmu, ga, gb = (gL * g).split(sizes)
+            gmu, ga, gb = gmu.to(types[0]), ga.to(types[1]), gb.to(types[2])
+        # (mu and beta may have any shape with their number of entries)
+        return (gmu if gmu.shape == smu else gmu.reshape(smu), ga.reshape(sa),
+                gb if gb.shape == sb else gb.reshape(sb), None, None, None, None)
 
 
 def hawkes_loglik(t, m, mu, alpha, beta, T, chunk_log2: int = 0) -> torch.Tensor:
