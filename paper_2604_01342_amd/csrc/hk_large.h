@@ -5,7 +5,7 @@
 #include "hk_internal.h"
 
 #ifndef HK_SEG
-#define HK_SEG 1024        // events per forward segment (one wave)
+#define HK_SEG 1024        // events per segment (the scan's elements)
 #endif
 #define HK_NARROW_MAX_M 64   // nodes up to which one kernel takes the forward pass and the gradient
 #define HK_F32_MIN_M 384   // nodes from which the dense gradient's U and K (and their product) are float32

@@ -15,15 +15,17 @@
 // Per chunk:
 //   agg      one wave per segment folds its events into (K_run, J_run)
 //   scan     one thread per node chains the segment maps -> carry-in per segment
-//   forward  a workgroup of two waves per segment replays its events 64 at a
-//            time (one per lane; each wave takes every other nonzero of the
-//            event's row of alpha, the first wave adds the partial sums and
-//            does the rest).  Each node keeps a lazily decayed record (tau_q, K_q, J_q)
-//            in LDS; lambda_i needs only the nonzeros of alpha's row m_i
-//            (R = alpha_{m_i,:} . K, eq. 3), read from a CSR copy of alpha,
-//            plus the same-batch events found through a per-node lane mask.
-//            It writes lambda_i / per-segment float64 partials and, for the
-//            gradient, per-event coefficients for the dense kernel.
+//   forward  a workgroup of four waves per segment (two with many nodes) replays
+//            its events 64 at a time, one per lane; a wave takes a share of each
+//            event's row of alpha, the first adds the partial sums and forms the
+//            intensity, another the compensator terms, another updates the
+//            records.  Each node keeps a record (K_q, J_q) in LDS, anchored at
+//            the segment's start (with a time of its own where the anchored
+//            exponents could overflow); lambda_i needs only the nonzeros of
+//            alpha's row m_i (R = alpha_{m_i,:} . K, eq. 3), read from a CSR copy
+//            of alpha, plus the same-batch events found through a per-node lane
+//            mask.  It writes lambda_i / per-segment float64 partials and, for
+//            the gradient, per-event coefficients for the dense kernel.
 //   bucket   the starts of the partition of the chunk's events by blocks of 16
 //            nodes (hk_bucket.hip)
 //   dense    dense dL/dalpha (first term of eq. 9, hk_dense.hip): per block of
@@ -1382,12 +1384,6 @@ void large_scan(LargeArgs& A, int32_t nseg, const float* beta_pt, hipStream_t st
                            A.seg_off, A.seg_offdec, A.gcarry, A.carry_seg, beta_pt);
 }
 
-// Several decay kernels (K > 1, shared decay per kernel; Background eq. 1,
-// gradients per kernel as in eqs. 8-10).  Per chunk: for each kernel k its
-// segment maps, carries and forward pass (R mode), then large_combine forms
-// lambda and the shared w_i = 1/lambda_i; with the gradient the chunk's events
-// are partitioned once and the dense dL/dalpha kernels run once per kernel
-// (decay beta_k, kernel k's state checkpoints and partial sums).
 // the dense gradient's partials of a sequence without events (otherwise the
 // first chunk stores them)
 static void dense_zero(const LargeArgs& A, ZeroList& Z) {
@@ -1412,10 +1408,15 @@ struct Fwd {
     }
 };
 
+// Several decay kernels (K > 1, shared decay per kernel; Background eq. 1,
+// gradients per kernel as in eqs. 8-10).  Per chunk: for each kernel k its
+// segment maps, carries and forward pass (R mode), then large_combine forms
+// lambda and the shared w_i = 1/lambda_i; with the gradient the chunk's events
+// are partitioned once and the dense dL/dalpha kernels run once per kernel
+// (decay beta_k, kernel k's state rows and partial sums).
 static hawkes_status run_large_multi(LargeArgs& A, hipStream_t st) {
     const int32_t M = A.M, K = A.K;
     const int64_t MM = (int64_t)M * M;
-    const unsigned gM = (unsigned)((M + 255) / 256);
     const size_t lds_agg = (size_t)2 * M * sizeof(double);
     const size_t lds_fwd = (size_t)M * (sizeof(uint64_t) + 2 * sizeof(double));
     if (allow_lds((const void*)large_seg_agg, lds_agg) != HAWKES_OK ||
@@ -1541,7 +1542,6 @@ hawkes_status run_large(LargeArgs& A, hipStream_t st) {
     if (A.narrow) return run_narrow(A, st);
     const int32_t M = A.M;
     const int64_t MM = (int64_t)M * M;
-    const unsigned gM = (unsigned)((M + 255) / 256);
     const size_t lds_agg = (size_t)2 * M * sizeof(double);
     const size_t lds_fwd = (size_t)M * (sizeof(uint64_t) + 2 * sizeof(double));
     if (allow_lds((const void*)large_seg_agg, lds_agg) != HAWKES_OK ||
