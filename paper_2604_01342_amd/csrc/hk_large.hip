@@ -1110,7 +1110,8 @@ static void large_rules(LargeArgs& A, const hawkes_problem* p, const hawkes_tuni
         // M = 4096) and 22 us beside them, a range the traffic of its partials
         // (both set by calls of 1 to 4 ranges, us: M = 2100, 2e5 events 915 /
         // 840 / 828 / 869, 6e4 events 598 / 608 / 625 / 646; M = 1450, 2e5
-        // 741 / 760 / 678 / 711; M = 3000, 3e5 1507 / 1479 / 1485 / 1565);
+        // 741 / 760 / 678 / 711; M = 3000, 3e5 1507 / 1479 / 1485 / 1565, all
+        // with the first chunk's partials cleared and read, 10 to 50 us more);
         // with some events for every wave and about 256 MiB of partials at most.
         const int64_t ev = A.n < A.CH ? A.n : A.CH, nbb = (int64_t)A.NB * A.NB;
         int64_t most = ev / (HK_PT_WAVE_EV * 16);

@@ -1002,14 +1002,17 @@ __device__ __forceinline__ int64_t rec_lower_bound(const uint32_t* __restrict__ 
 // Blocks with sb == 0 also sum w_i per target, blocks with rb == 0 count the
 // events per source.
 //
-// Bound by the vector ALU: 25 instructions per slab event and 128 targets (12
-// decays, 4 for the own event joined meanwhile, 4 for the event's step and
-// column, 5 of the window's share); the two LDS adds are hidden.
-// M = 4096, 2^20 events: 2.40 ms a launch; 2.88 with blocks of 64 targets and
-// columns (twice the own events and window set-ups per slab event and target)
-// and float32 exponentials with their correction terms; 2.72 without the
-// rotating priority.  M = 100, 2e5 events: 35 us, 204 with one wave for every
-// segment of 1024 events.
+// Bound by the vector ALU (active 77% of the SIMDs' clocks) and the LDS (74% of the
+// CUs'), side by side: 25 vector instructions per slab event and 128 targets (12
+// decays, 2 for the own event joined meanwhile, 4 for the event's step and
+// column, the rest of the window's share) and 2.6 LDS instructions, two of them
+// the adds.
+// M = 4096, 2^20 events: 2.30 ms a launch; 2.40 with an own event's target in 7
+// bits of its weight and, for the first chunk, its partials read; 2.88 with
+// blocks of 64 targets and columns (twice the own events and window set-ups per
+// slab event and target) and float32 exponentials with their correction terms;
+// 2.72 without the rotating priority.  M = 100, 2e5 events: 35 us, 204 with one
+// wave for every segment of 1024 events.
 __global__ __launch_bounds__(64 * PT_DW) void pt_dense(int64_t c0, int64_t c1, int64_t n, double T, int32_t M, int32_t NB,
                                                    int32_t ER, int32_t seg, int32_t nseg, int32_t nsegb,
                                                    const double* __restrict__ t, const float* __restrict__ beta,

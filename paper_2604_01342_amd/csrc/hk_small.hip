@@ -954,7 +954,7 @@ __global__ __launch_bounds__(1024) void small_reduce2(int32_t S, int64_t n_chunk
 // HK_GL_ITEMS MP items (more waves and a shorter chain per event: 48 sequences
 // of 100 to 2000 events 21 / 15 us with two / four lanes; 1e6 events, M = 3, 102
 // / 95 a call); beyond, two lanes with the block in registers (the chip is full;
-// bound by the vector ALU, busy 91% of the time, where four lanes do more in
+// bound by the vector ALU, busy 93% of the time, where four lanes do more in
 // all: 6.3e7 events in 4096 sequences 1004 / 1116 us; 3e6 events, M = 4, 161 /
 // 163 a call).
 #define HK_GL_ITEMS 4096
