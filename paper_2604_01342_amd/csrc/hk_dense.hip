@@ -123,7 +123,8 @@ __global__ __launch_bounds__(64 * HK_PW) void dense_prep(int64_t c0, int32_t nev
                                                          int32_t* __restrict__ plist) {
     constexpr int NBK = HK_SEG >> BL;            // blocks per segment
     constexpr int NBT = HK_SEG / 64 / HK_PW;     // batches per wave
-    static_assert(NBT * 64 * HK_PW == HK_SEG && BL >= 6 && BL <= 10, "whole batches per wave, whole blocks per segment");
+    static_assert(NBT * 64 * HK_PW == HK_SEG && BL >= 6 && BL <= 10,
+                  "whole batches per wave, whole blocks per segment");
     extern __shared__ double lds[];
     double* Kl = lds;
     double* Ul = lds + M;
@@ -279,7 +280,8 @@ __global__ __launch_bounds__(64 * HK_PW) void dense_prep(int64_t c0, int32_t nev
         // pair record, at its place by bank (past the events: last)
         const int col = mk + M * (lane & (rep - 1));
         const int32_t pp = base + bank_place(v ? (col & 15) : 16, lt);
-        prec[pp] = v ? make_uint2(((uint32_t)(i & ((1 << BL) - 1)) << 16) | (uint32_t)(8 * col), (uint32_t)__float_as_int(bj[u]))
+        prec[pp] = v ? make_uint2(((uint32_t)(i & ((1 << BL) - 1)) << 16) | (uint32_t)(8 * col),
+                                  (uint32_t)__float_as_int(bj[u]))
                      : make_uint2(0xffff0000u, 0u);
     }
     if (!krow) return;
@@ -542,8 +544,8 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
             constexpr int GC = 256 / sizeof(RT);
             const int nm = (((CW + GC - 1) / GC) - wv + HK_TGW - 1) / HK_TGW;
             auto product = [&](auto gm) {
-                tile_product<decltype(gm)::value>(urow, krow, Mp, rb * 16, cb0, CW, M - cb0 < CW ? M - cb0 : CW, rA, rB, wv,
-                                                        lane, GP);
+                tile_product<decltype(gm)::value>(urow, krow, Mp, rb * 16, cb0, CW, M - cb0 < CW ? M - cb0 : CW, rA,
+                                                  rB, wv, lane, GP);
             };
             if (rA >= rB || nm <= 0) {
             } else if (nm == 1) {
@@ -685,90 +687,90 @@ __global__ __launch_bounds__(64 * HK_TW) void dense_tiles(int64_t c0, int32_t ne
                 const int32_t oL0 = oL;   // the block's first own record
                 const int k0 = k;
                 for (bool again = false;; again = true) {
-                for (;;) {
-                    const uint64_t in = __ballot(ob_ == blk) & todo;
-                    const int kn = k + __builtin_popcountll(in);
-                    if (kn > k && !w) {
-                        for (int x = k; x < kn; ++x) {
-                            const int pk = rl_i(pack, x);
-                            const double c = (double)rl_f(oc.cw.x, x);
-                            char* row = tile + (pk >> 10);
-                            const int pi = pk & 1023;
-                            if constexpr (MC) {
-                                // a list's groups in event order: up to the
-                                // first without a record before the event
+                    for (;;) {
+                        const uint64_t in = __ballot(ob_ == blk) & todo;
+                        const int kn = k + __builtin_popcountll(in);
+                        if (kn > k && !w) {
+                            for (int x = k; x < kn; ++x) {
+                                const int pk = rl_i(pack, x);
+                                const double c = (double)rl_f(oc.cw.x, x);
+                                char* row = tile + (pk >> 10);
+                                const int pi = pk & 1023;
+                                if constexpr (MC) {
+                                    // a list's groups in event order: up to the
+                                    // first without a record before the event
 #pragma unroll
-                                for (int g = 0; g < NG; ++g) {
-                                    const bool on = pl[g] < pi;
-                                    if (__ballot(on) == 0) break;
-                                    if (on) atomicAdd(reinterpret_cast<double*>(row + col[g]), c * bj[g]);
+                                    for (int g = 0; g < NG; ++g) {
+                                        const bool on = pl[g] < pi;
+                                        if (__ballot(on) == 0) break;
+                                        if (on) atomicAdd(reinterpret_cast<double*>(row + col[g]), c * bj[g]);
+                                    }
+                                    continue;
                                 }
-                                continue;
-                            }
-                            // the records before the event, group by group up
-                            // to its own; the others' lanes add a zero (their
-                            // high word cleared: at most a denormal), which
-                            // costs one select instead of an exec mask and a
-                            // branch
-                            auto add = [&](int g) __attribute__((always_inline)) {
-                                const double v = c * bj[g];
-                                const int hi = pl[g] < pi ? __double2hiint(v) : 0;
-                                atomicAdd(reinterpret_cast<double*>(row + col[g]),
-                                          __hiloint2double(hi, __double2loint(v)));
-                            };
-                            add(0);
-                            if (NG > 1 && pi >= 64) {
-                                add(NG > 1 ? 1 : 0);
-                                if (NG > 2 && pi >= 128) {
-                                    add(NG > 2 ? 2 : 0);
-                                    if (pi >= 192) add(NG > 2 ? 3 : 0);
-                                }
-                            }
-                        }
-                    } else if (kn > k) {
-                        // wide block (the anchored factors could leave float32
-                        // range): exact decays per pair
-                        const int64_t b0 = c0 + ((int64_t)blk << BL);
-                        double tr[NG];
-#pragma unroll
-                        for (int g = 0; g < NG; ++g) tr[g] = t[pl[g] < (1 << BL) ? b0 + pl[g] : b0];
-                        const double town = t[c0 + (int32_t)(oc.key >> 4)];
-                        const double cwd = bet * (double)oc.cw.y;
-                        for (int x = k; x < kn; ++x) {
-                            const int pk = rl_i(pack, x);
-                            char* row = tile + (pk >> 10);
-                            const int pi = pk & 1023;
-                            const double tk = rl_d(town, x), ck = rl_d(cwd, x);
-#pragma unroll
-                            for (int g = 0; g < NG; ++g)
-                                if (pl[g] < pi)
+                                // the records before the event, group by group up
+                                // to its own; the others' lanes add a zero (their
+                                // high word cleared: at most a denormal), which
+                                // costs one select instead of an exec mask and a
+                                // branch
+                                auto add = [&](int g) __attribute__((always_inline)) {
+                                    const double v = c * bj[g];
+                                    const int hi = pl[g] < pi ? __double2hiint(v) : 0;
                                     atomicAdd(reinterpret_cast<double*>(row + col[g]),
-                                              ck * (double)exp2_f64arg((tr[g] - tk) * bl2));
+                                              __hiloint2double(hi, __double2loint(v)));
+                                };
+                                add(0);
+                                if (NG > 1 && pi >= 64) {
+                                    add(NG > 1 ? 1 : 0);
+                                    if (NG > 2 && pi >= 128) {
+                                        add(NG > 2 ? 2 : 0);
+                                        if (pi >= 192) add(NG > 2 ? 3 : 0);
+                                    }
+                                }
+                            }
+                        } else if (kn > k) {
+                            // wide block (the anchored factors could leave float32
+                            // range): exact decays per pair
+                            const int64_t b0 = c0 + ((int64_t)blk << BL);
+                            double tr[NG];
+#pragma unroll
+                            for (int g = 0; g < NG; ++g) tr[g] = t[pl[g] < (1 << BL) ? b0 + pl[g] : b0];
+                            const double town = t[c0 + (int32_t)(oc.key >> 4)];
+                            const double cwd = bet * (double)oc.cw.y;
+                            for (int x = k; x < kn; ++x) {
+                                const int pk = rl_i(pack, x);
+                                char* row = tile + (pk >> 10);
+                                const int pi = pk & 1023;
+                                const double tk = rl_d(town, x), ck = rl_d(cwd, x);
+#pragma unroll
+                                for (int g = 0; g < NG; ++g)
+                                    if (pl[g] < pi)
+                                        atomicAdd(reinterpret_cast<double*>(row + col[g]),
+                                                  ck * (double)exp2_f64arg((tr[g] - tk) * bl2));
+                            }
                         }
+                        k = kn;
+                        if (k < 64 || oL + 64 >= O1) break;
+                        // oc used up: continue in on
+                        oc = on;
+                        oL += 64;
+                        k = 0;
+                        own_load(on, oL + 64);
+                        if (!again) own_sums(oc, oL);
+                        own_prep();
                     }
-                    k = kn;
-                    if (k < 64 || oL + 64 >= O1) break;
-                    // oc used up: continue in on
-                    oc = on;
-                    oL += 64;
-                    k = 0;
-                    own_load(on, oL + 64);
-                    if (!again) own_sums(oc, oL);
-                    own_prep();
-                }
-                if (!MC || gx + NG >= gy) break;
-                // a list of more groups than are held: the next ones, and the
-                // block's own records again
-                gx += NG;
-                blk_load(rc, blk, gx, gy);
-                unpack();
-                if (oL != oL0) {
-                    oL = oL0;
-                    own_load(oc, oL);
-                    own_load(on, oL + 64);
-                    own_prep();
-                }
-                k = k0;
+                    if (!MC || gx + NG >= gy) break;
+                    // a list of more groups than are held: the next ones, and the
+                    // block's own records again
+                    gx += NG;
+                    blk_load(rc, blk, gx, gy);
+                    unpack();
+                    if (oL != oL0) {
+                        oL = oL0;
+                        own_load(oc, oL);
+                        own_load(on, oL + 64);
+                        own_prep();
+                    }
+                    k = k0;
                 }
                 rc = rn;
                 gx = nx;

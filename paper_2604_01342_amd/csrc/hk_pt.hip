@@ -1004,8 +1004,8 @@ __device__ __forceinline__ int64_t rec_lower_bound(const uint32_t* __restrict__ 
 //
 // Bound by the vector ALU (active 77% of the SIMDs' clocks) and the LDS (74% of the
 // CUs'), side by side: 25 vector instructions per slab event and 128 targets (12
-// decays, 2 for the own event joined meanwhile, 4 for the event's step and
-// column, the rest of the window's share) and 2.6 LDS instructions, two of them
+// decays, 4 for the own event joined meanwhile, 4 for the event's step and
+// column, 5 of the window's share) and 2.6 LDS instructions, two of them
 // the adds.
 // M = 4096, 2^20 events: 2.30 ms a launch; 2.40 with an own event's target in 7
 // bits of its weight and, for the first chunk, its partials read; 2.88 with
